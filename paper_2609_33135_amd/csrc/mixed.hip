@@ -7,7 +7,7 @@
 // head) counter when its state is written; the last one merges the group's
 // query heads (log-sum-exp, the same arithmetic as the separate merge kernel)
 // and resets the counter, so the step needs no second launch.  A workgroup is
-// 512 threads; a prefill item uses about 98 KB of LDS for its two tile buffers, a
+// 512 threads; a prefill item uses about 105 KB of LDS for its two tile buffers, a
 // group of eight decode items none (their K and V go straight to registers).
 //
 // Placement: a prefill workgroup holds a whole compute unit (its LDS and all
@@ -23,8 +23,6 @@ namespace mpfa {
 
 namespace {
 
-constexpr int kMixedLds = sizeof(PrefillSmemT<kPvFp8>) * 2;
-
 // Blocks are dealt to the 8 XCDs round-robin, so the grid is laid out in rounds
 // of 8 consecutive blocks.  Decode rounds (8 groups of 8 decode work items)
 // sit at round indices first, first + stride, ...; prefill items fill the
@@ -34,7 +32,7 @@ constexpr int kMixedLds = sizeof(PrefillSmemT<kPvFp8>) * 2;
 // of the prefill items holds as in the separate launch.
 template <bool SMOOTH, bool MX>
 __global__ __launch_bounds__(512, 1) void mixed_kernel(MixedParams m) {
-  __shared__ __attribute__((aligned(16))) uint8_t lds[kMixedLds];
+  __shared__ __attribute__((aligned(16))) PrefillSmemT<MX, kPvFp8> lds;
   const int i = blockIdx.x, r = i >> 3;
   // decode round k sits at round first + k * stride (k < n_dec_rounds)
   const int rel = r - m.first;
@@ -43,8 +41,7 @@ __global__ __launch_bounds__(512, 1) void mixed_kernel(MixedParams m) {
   if (!is_dec) {
     const int bid = i - 8 * dec_before;
     if (bid >= m.n_pre_blocks) return;
-    prefill_item<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8>(m.pre, bid,
-                                                             reinterpret_cast<PrefillSmemT<kPvFp8>*>(lds));
+    prefill_item<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8, 8>(m.pre, bid, lds);
     return;
   }
   // decode group (round, lane of the round): wave w takes item 8 * group + w =

@@ -12,6 +12,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
@@ -159,6 +160,21 @@ __device__ __forceinline__ f16x8 dequant8(uint32_t codes, ScaleSplit s) {
   return (f16x8){a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
 }
 
+// Eight E2M1 codes times an E4M3 scale held in FP16: both factors and the
+// product (see above) are exact in FP16.
+__device__ __forceinline__ f16x8 dequant8h(uint32_t codes, _Float16 scale) {
+  const f16x2 m = {scale, scale};
+  f16x2 a = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 0) * m;
+  f16x2 b = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 1) * m;
+  f16x2 c = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 2) * m;
+  f16x2 d = __builtin_amdgcn_cvt_scalef32_pk_f16_fp4(codes, 1.0f, 3) * m;
+  return (f16x8){a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
+}
+// The two E4M3 codes in the low bytes of w as FP16 (exact; NaN codes stay NaN).
+__device__ __forceinline__ f16x2 e4m3_pair_f16(uint32_t w) {
+  return __builtin_amdgcn_cvt_scalef32_pk_f16_fp8((int)w, 1.0f, false);
+}
+
 // ---------------------------------------------------------------------------
 // Matrix instructions (16x16 output tiles, 64-lane wavefront).
 // Operand layout (verified on gfx950): lane l supplies row (A) / column (B)
@@ -168,12 +184,30 @@ __device__ __forceinline__ f16x8 dequant8(uint32_t codes, ScaleSplit s) {
 __device__ __forceinline__ f32x4 mfma_f16(f16x8 a, f16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0);
 }
-__device__ __forceinline__ f32x4 mfma_bf16(bf16x8 a, bf16x8 b, f32x4 c) {
-  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-}
 // FP8 E4M3 x FP8 E4M3, K = 128, unit block scales (E8M0 127 = 2^0).
 __device__ __forceinline__ f32x4 mfma_fp8(i32x8 a, i32x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(a, b, c, 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
+}
+
+// The 32x32 forms: lane l supplies row (A) / column (B) l % 32 and the
+// contiguous slice l / 32 of the reduction dimension (8 values of 16, or 32 of
+// 64); accumulator register r of lane l is row 8*(r/4) + 4*(l/32) + r%4 of
+// column l % 32.
+__device__ __forceinline__ f32x16 mfma32_f16(f16x8 a, f16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 mfma32_bf16(bf16x8 a, bf16x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x16 mfma32_fp8(i32x8 a, i32x8 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(a, b, c, 0, 0, 0, 0x7F7F7F7F, 0, 0x7F7F7F7F);
+}
+// byte SEL of scale_a holds this lane's E8M0 scale of A, the low byte of scale_b that of B
+template <int SEL>
+__device__ __forceinline__ f32x16 mfma32_fp4(u32x4 a, u32x4 b, f32x16 c, int scale_a, int scale_b) {
+  const i32x8 av = {(int)a[0], (int)a[1], (int)a[2], (int)a[3], 0, 0, 0, 0};
+  const i32x8 bv = {(int)b[0], (int)b[1], (int)b[2], (int)b[3], 0, 0, 0, 0};
+  return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(av, bv, c, 4, 4, SEL, scale_a, 0, scale_b);
 }
 
 // Scaled FP4 MFMA (MXFP4): A and B hold 32 E2M1 values per lane (16 bytes in
@@ -203,6 +237,12 @@ __device__ __forceinline__ uint32_t pack_fp8x4(float a, float b, float c, float 
 __device__ __forceinline__ float wave_max16(float x) {
   const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   x = fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1]));
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+// Maximum over the two lanes l, l^32.
+__device__ __forceinline__ float wave_max32(float x) {
   const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }

@@ -1,34 +1,35 @@
 // prefill.hip -- causal QK4PV8 prefill for gfx950 (Algorithm 1 main loop).
 //
 // One workgroup = 8 waves = 256 query rows of one query head; each wave owns
-// 32 rows (two 16-row MFMA column blocks).  Per 128-key tile (visited from the
+// 32 rows, the columns of one 32x32 MFMA.  Per 128-key tile (visited from the
 // block's last tile down to tile 0, Sec. 4.1):
 //   * the workgroup stages the tile in LDS: NVFP4 K dequantized once to exact
 //     FP16 (group scale applied, tensor scale factored out), FP8 V in its
 //     channel-major page layout, and the compensation vector Delta_S;
-//   * each wave computes S^T = K Q^T on FP16 MFMA (16x16x32) starting from
+//   * each wave computes S^T = K Q^T on FP16 MFMA (32x32x16) starting from
 //     the rank-one term 1 Delta_S^T (Sec. 4.3 Eq. 11): loaded from LDS as the
 //     accumulator input, or (MPFA_SEED_MFMA) formed by one BF16 rank-one MFMA
-//     per 16x16 block as in Sec. 5.2;
+//     per 32x32 block as in Sec. 5.2;
 //   * mask, row max, P = 2^(lambda (S - m) + log2 448), row sum of the FP32 P,
 //     FP8 conversion in registers; the S^T accumulator layout is already the
 //     B-operand layout of the FP8 PV MFMA (O^T = V^T P^T), so P never leaves
 //     registers;
 //   * O^T rescale (skipped when no row maximum moved) and FP8 MFMA
-//     (16x16x128) accumulation.
-// The key order inside a 16-row MFMA block is permuted so that the 32 keys a
-// lane holds after the QK product are contiguous: MFMA row r of key block mb
-// is key 32*(r/4) + 4*mb + r%4.
+//     (32x32x64) accumulation.
+// The key order inside a 32-row MFMA block is permuted so that the 32 keys a
+// lane holds for a PV MFMA are contiguous (tile_key).
 #include "prefill_body.h"
 
 namespace mpfa {
 
 namespace {
 
+constexpr int kWaves = 8, kThreads = kWaves * 64;
+
 template <int SEED, bool MX, int PV, int ABL = 0>
 __global__ __launch_bounds__(kThreads, 1) void prefill_kernel(PrefillParams p) {
-  __shared__ __attribute__((aligned(16))) PrefillSmemT<PV> smem[2];
-  prefill_item<SEED, MX, PV, ABL>(p, blockIdx.x, smem);
+  __shared__ __attribute__((aligned(16))) PrefillSmemT<MX, PV> smem;
+  prefill_item<SEED, MX, PV, kWaves, ABL>(p, blockIdx.x, smem);
 }
 
 #ifdef MPFA_ABLATION_BUILD
@@ -83,7 +84,5 @@ hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream) {
   }
   return hipGetLastError();
 }
-
-int prefill_query_rows_per_block() { return kQRows; }
 
 }  // namespace mpfa
