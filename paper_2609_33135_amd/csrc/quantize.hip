@@ -165,6 +165,75 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(QuantParams p) {
   }
 }
 
+// The same for few blocks: one wave per (head, block, sequence), two channels
+// per lane and 32 tokens in flight.  A block is a serial walk over its tokens,
+// so with too few workgroups to fill the chip its latency counts: 16 lanes a
+// head with 8 channels each spend 20 us on the 4096 vector operations and 8
+// round trips of a block, this shape 2 channels' 1024 and 4 (see launch_quantize
+// for the line between the two).  Per channel the tokens add in the same order.
+__global__ __launch_bounds__(64) void stats_partial_wave_kernel(QuantParams p) {
+  constexpr int kAhead = 32;
+  const int hh = blockIdx.x, blk = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
+  const int64_t t0 = p.cu_seqlens[b];
+  const int n = p.cu_seqlens[b + 1] - (int)t0;
+  const int nblk = (n + 127) >> 7;
+  if (blk >= nblk) return;
+  const StatsShape ss = stats_shape(p);
+  const int tb = blk * 128, cnt = min(n - tb, 128);
+  if (nblk >= 2 && blk == 0 && lane == 0)   // arrival counter of stats_final_kernel
+    reinterpret_cast<uint32_t*>(fin_scratch(p, t0, ss.hs))[hh] = 0u;
+  const bool isq = hh < p.h_q;
+  const int H = isq ? p.h_q : p.h_kv;
+  const uint32_t* src =
+      reinterpret_cast<const uint32_t*>((isq ? p.q : p.k) + ((t0 + tb) * H + (isq ? hh : hh - p.h_q)) * kD) + lane;
+  const int64_t stride = (int64_t)H * (kD / 2);
+  float s0 = 0.0f, s1 = 0.0f, x0 = -INFINITY, x1 = -INFINITY, m0 = INFINITY, m1 = INFINITY;
+  for (int t = 0; t < cnt; t += kAhead) {
+    uint32_t w[kAhead];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) w[j] = src[(int64_t)min(t + j, cnt - 1) * stride];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j) {
+      const float a = __uint_as_float(w[j] << 16), c = __uint_as_float(w[j] & 0xFFFF0000u);
+      if (t + j < cnt) {
+        s0 += a;
+        s1 += c;
+      }
+      // past the block's end the last token repeats: no change to max and min
+      x0 = fmaxf(x0, a);
+      x1 = fmaxf(x1, c);
+      m0 = fminf(m0, a);
+      m1 = fminf(m1, c);
+    }
+  }
+  if (nblk == 1) {
+    // one block: its partial sum is the total (0 + partial, exact)
+    uint16_t* mrow = mean_row(p, b, hh) + 2 * lane;
+    uint16_t v0 = 0, v1 = 0;
+    if (ss.want_sum) {
+      v0 = bf16_rne(__fdiv_rn(s0, (float)n));
+      v1 = bf16_rne(__fdiv_rn(s1, (float)n));
+    } else if (!p.compute_stats && p.smooth) {
+      v0 = mrow[0];
+      v1 = mrow[1];
+    }
+    if (p.compute_stats) {
+      mrow[0] = v0;
+      mrow[1] = v1;
+    }
+    const float u0 = bf16_to_f32(v0), u1 = bf16_to_f32(v1);
+    float amax = fmaxf(fmaxf(__builtin_fabsf(x0 - u0), __builtin_fabsf(m0 - u0)),
+                       fmaxf(__builtin_fabsf(x1 - u1), __builtin_fabsf(m1 - u1)));
+    for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+    if (lane == 0) write_tscale(p, b, hh, amax);
+  } else {
+    float* part = partial_ptr(p, t0, nblk, blk, ss.hs) + hh * kD + 2 * lane;
+    *reinterpret_cast<float2*>(part) = make_float2(s0, s1);
+    *reinterpret_cast<float2*>(part + ss.hs * kD) = make_float2(x0, x1);
+    *reinterpret_cast<float2*>(part + 2 * ss.hs * kD) = make_float2(m0, m1);
+  }
+}
+
 // stats_final_kernel: one workgroup of 256 threads per (head, 32-channel
 // slice, sequence), so that the partials of one head are read by four compute
 // units.  The slice's partials arrive in LDS 256 blocks at a time (coalesced
@@ -267,6 +336,56 @@ __global__ __launch_bounds__(kFinThreads) void stats_final_kernel(QuantParams p)
       }
     }
   }
+}
+
+// The same for sequences of few blocks: one workgroup of 128 threads per (head,
+// sequence), one channel per thread, its partials read straight from memory
+// (kShortBatch blocks in flight) and added in block order.  No LDS chunk, no
+// arrival counters: with at most kShortBlocks blocks the reads are a few round
+// trips, where the kernel above spends its time on whole 256-block chunks.
+constexpr int kShortBlocks = 64;
+constexpr int kShortBatch = 32;
+
+__global__ __launch_bounds__(kD) void stats_final_short_kernel(QuantParams p) {
+  __shared__ float wave_amax[2];
+  const int hh = blockIdx.x, b = blockIdx.y, c = threadIdx.x;
+  const int64_t t0 = p.cu_seqlens[b];
+  const int n = p.cu_seqlens[b + 1] - (int)t0;
+  const int nblk = (n + 127) >> 7;
+  if (p.need_partials && nblk == 1) return;   // finished by stats_partial_kernel
+  const StatsShape ss = stats_shape(p);
+  const bool have = p.need_partials && nblk >= 2;
+  float tot = 0.0f, mx = -INFINITY, mn = INFINITY;
+  if (have) {
+    for (int blk0 = 0; blk0 < nblk; blk0 += kShortBatch) {
+      float s[kShortBatch], x[kShortBatch], m[kShortBatch];
+#pragma unroll
+      for (int j = 0; j < kShortBatch; ++j) {
+        const float* part = partial_ptr(p, t0, nblk, min(blk0 + j, nblk - 1), ss.hs) + hh * kD + c;
+        s[j] = part[0];
+        x[j] = part[ss.hs * kD];
+        m[j] = part[2 * ss.hs * kD];
+      }
+#pragma unroll
+      for (int j = 0; j < kShortBatch; ++j)
+        if (blk0 + j < nblk) {
+          tot += s[j];
+          mx = fmaxf(mx, x[j]);
+          mn = fminf(mn, m[j]);
+        }
+    }
+  }
+  uint16_t* mrow = mean_row(p, b, hh);
+  uint16_t m = 0;
+  if (have && ss.want_sum) m = bf16_rne(__fdiv_rn(tot, (float)n));
+  else if (!p.compute_stats && p.smooth) m = mrow[c];
+  if (p.compute_stats) mrow[c] = m;
+  const float mu = bf16_to_f32(m);
+  float amax = have ? fmaxf(__builtin_fabsf(mx - mu), __builtin_fabsf(mn - mu)) : 0.0f;
+  for (int off = 32; off >= 1; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+  if ((c & 63) == 0) wave_amax[c >> 6] = amax;
+  __syncthreads();
+  if (c == 0) write_tscale(p, b, hh, fmaxf(wave_amax[0], wave_amax[1]));
 }
 
 // NVFP4 quantization (Sec. 2.1 Eq. 1) of a 16-channel group of centered FP32
@@ -387,6 +506,29 @@ __device__ __forceinline__ float group_max(float a) {
   return a;
 }
 
+// Codes and scale of one lane's 8 centered channels (c8: which of the row's 16
+// lanes): every lane of a group derives the group's scale.
+template <bool MX>
+__device__ __forceinline__ uint32_t encode_lane(const float* xc, float t, const float* rcp_sd, uint32_t* scale_code) {
+  float a = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a = fmaxf(a, __builtin_fabsf(xc[i]));
+  a = group_max<MX>(a);
+  if (MX) {
+    int e = -127;
+    if (a > 0.0f) e = max(-127, min(127, ilog2f(a) - 2));
+    *scale_code = (uint32_t)(e + 127);
+    const float pw = __builtin_ldexpf(1.0f, max(e, -126));
+    uint32_t w = 0u;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) w = fp4_pair(w, xc[2 * j], xc[2 * j + 1], pw, j);
+    return w;
+  }
+  const Nv4Scale s = nvfp4_scale(a, t, rcp_sd);
+  *scale_code = s.code;
+  return nvfp4_encode8(xc, s);
+}
+
 // Q rows: one lane per 8 channels (16 bytes) of a row, so a wave reads and
 // writes 4 whole rows; the lanes of a group (2 for NVFP4, 4 for MXFP4) share
 // its amax.  Each lane has U units in flight before it quantizes them.
@@ -413,25 +555,9 @@ __device__ __forceinline__ void quant_q_rows(const QuantParams& p, const uint8_t
         const int r = u >> 4, c8 = u & 15, h = r % H, g = c8 / L;
         float xc[8];
         center8(v[k], *reinterpret_cast<const uint4*>(mean_base + h * kMeanStride + c8 * 16), xc);
-        float a = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) a = fmaxf(a, __builtin_fabsf(xc[i]));
-        a = group_max<MX>(a);
         const int64_t row = tok0 * H + r;
-        uint32_t w, sc;
-        if (MX) {
-          int e = -127;
-          if (a > 0.0f) e = max(-127, min(127, ilog2f(a) - 2));
-          sc = (uint32_t)(e + 127);
-          const float pw = __builtin_ldexpf(1.0f, max(e, -126));
-          w = 0u;
-#pragma unroll
-          for (int j = 0; j < 4; ++j) w = fp4_pair(w, xc[2 * j], xc[2 * j + 1], pw, j);
-        } else {
-          const Nv4Scale s = nvfp4_scale(a, tscale[h], rcp_sd);
-          sc = s.code;
-          w = nvfp4_encode8(xc, s);
-        }
+        uint32_t sc;
+        const uint32_t w = encode_lane<MX>(xc, MX ? 1.0f : tscale[h], rcp_sd, &sc);
         *reinterpret_cast<uint32_t*>(p.q_codes + row * 64 + c8 * 4) = w;
         if (c8 % L == 0) {
           p.q_scales[row * 8 + g] = (uint8_t)sc;
@@ -667,6 +793,323 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams p) {
   }
 }
 
+// ---------------------------------------------------------------------------
+// Few tokens: one workgroup (256 threads) per (64-token chunk, KV head with its
+// group of query heads, sequence).  Everything a chunk writes for one KV head
+// depends on that head group alone, so the chunk splits over the KV heads.
+// quantize_kernel above is the better one when the chunks alone fill the chip;
+// with few chunks its long serial lanes show (a K row there is one lane's work:
+// 8 groups, then a 128-step chain per query head, about 40 us however few the
+// rows).  Here 16 lanes share a K row as they do a Q row, the centered values
+// go to LDS, and one lane per (token, query head) runs its Delta_S chain.
+// Same arithmetic in the same order: the bytes are those of quantize_kernel.
+// ---------------------------------------------------------------------------
+constexpr int kMaxGroupLds = 16;             // query heads per KV head the group kernels take
+constexpr int kKcStride = kD + 4;            // floats per centered K row in LDS (padded: rows on distinct banks)
+
+struct GroupSmem {
+  float kc[kChunk * kKcStride];              // centered K rows
+  float rcp_sd[128];
+  float ts[kMaxGroupLds + 1];                // tensor scales: the group's Q heads, then K
+  int page_start;                            // 1: the chunk's tokens are slots 0, 1, ... of one page, in order
+  __attribute__((aligned(16))) uint8_t mean[(kMaxGroupLds + 1) * kMeanStride];   // BF16 mean rows, Q heads then K
+};
+
+// V of 16 tokens (qq .. qq + 15 of the chunk) and channels 2cp, 2cp + 1 of head
+// h: FP8 into the page rows (page_run: all 64 slots present), and the
+// characterization copies.
+__device__ __forceinline__ void quant_v_part(const QuantParams& p, int64_t tok0, int cnt, int64_t page, int h, int cp,
+                                             int qq, bool page_run, const float* rcp_sd) {
+  const uint32_t* src = reinterpret_cast<const uint32_t*>(p.v + (tok0 * p.h_kv + h) * kD) + cp;
+  const int64_t tstride = (int64_t)p.h_kv * (kD / 2);
+  const int64_t crow = (page * p.h_kv + h) * kD + 2 * cp;   // channel row 2cp; 2cp+1 follows
+  const int64_t aux_scales = p.num_pages * p.h_kv * kD * 32;   // NVFP4 scale plane offset
+  uint32_t w[16];
+#pragma unroll
+  for (int j = 0; j < 16; ++j) w[j] = qq + j < cnt ? src[(int64_t)(qq + j) * tstride] : 0u;
+  if (page_run) {
+    u32x4 r0, r1;   // bytes of channels 2cp and 2cp+1
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t* wq = w + 4 * q;
+      uint32_t a = fp8_sat_pair(0u, __uint_as_float(wq[0] << 16), __uint_as_float(wq[1] << 16), false);
+      a = fp8_sat_pair(a, __uint_as_float(wq[2] << 16), __uint_as_float(wq[3] << 16), true);
+      uint32_t c = fp8_sat_pair(0u, __uint_as_float(wq[0] & 0xFFFF0000u), __uint_as_float(wq[1] & 0xFFFF0000u), false);
+      c = fp8_sat_pair(c, __uint_as_float(wq[2] & 0xFFFF0000u), __uint_as_float(wq[3] & 0xFFFF0000u), true);
+      r0[q] = a;
+      r1[q] = c;
+    }
+    *reinterpret_cast<u32x4*>(p.v_codes + crow * kPage + qq) = r0;
+    *reinterpret_cast<u32x4*>(p.v_codes + (crow + 1) * kPage + qq) = r1;
+    if (p.pv == 1) {   // BF16 rows: 16 keys of each channel, 32 bytes
+      uint32_t b0[8], b1[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        b0[j] = (w[2 * j] & 0xFFFFu) | (w[2 * j + 1] << 16);
+        b1[j] = (w[2 * j] >> 16) | (w[2 * j + 1] & 0xFFFF0000u);
+      }
+      uint16_t* a16 = reinterpret_cast<uint16_t*>(p.v_aux) + crow * kPage + qq;
+      *reinterpret_cast<u32x4*>(a16) = (u32x4){b0[0], b0[1], b0[2], b0[3]};
+      *reinterpret_cast<u32x4*>(a16 + 8) = (u32x4){b0[4], b0[5], b0[6], b0[7]};
+      *reinterpret_cast<u32x4*>(a16 + kPage) = (u32x4){b1[0], b1[1], b1[2], b1[3]};
+      *reinterpret_cast<u32x4*>(a16 + kPage + 8) = (u32x4){b1[4], b1[5], b1[6], b1[7]};
+    }
+  }
+  if (p.pv == 2) {   // one NVFP4 group per channel: these 16 keys (absent ones zero)
+    float x0[16], x1[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      x0[j] = __uint_as_float(w[j] << 16);
+      x1[j] = __uint_as_float(w[j] & 0xFFFF0000u);
+    }
+    uint32_t sc0, sc1;
+    const uint64_t c0 = nvfp4_group(x0, 1.0f, rcp_sd, &sc0);
+    const uint64_t c1 = nvfp4_group(x1, 1.0f, rcp_sd, &sc1);
+    *reinterpret_cast<uint64_t*>(p.v_aux + crow * 32 + qq / 2) = c0;
+    *reinterpret_cast<uint64_t*>(p.v_aux + (crow + 1) * 32 + qq / 2) = c1;
+    p.v_aux[aux_scales + crow * 4 + qq / 16] = (uint8_t)sc0;
+    p.v_aux[aux_scales + (crow + 1) * 4 + qq / 16] = (uint8_t)sc1;
+  }
+}
+
+// Parts of a head group's work, which need nothing of each other: separate
+// workgroups take one part each (their latencies then run side by side: a chunk
+// of 64 tokens takes 18 us in one workgroup whatever the number of chunks).
+enum GroupPart { kPartK = 1, kPartQ = 2, kPartV = 4, kPartAll = 7 };   // kPartK: K rows and Delta_S
+
+// Quantization and cache write of cnt (1..64) tokens from tok0 for KV head hk and
+// its query heads; sm.mean, sm.ts, sm.rcp_sd and sm.page_start are filled.
+template <bool MX>
+__device__ __forceinline__ void quant_group(const QuantParams& p, GroupSmem& sm, int64_t tok0, int cnt, int hk,
+                                            int parts) {
+  constexpr int L = MX ? 4 : 2;          // lanes per quantization group
+  constexpr int U = 8;                   // Q units per lane in flight
+  const int grp = p.h_q / p.h_kv, tid = threadIdx.x;
+
+  // K rows: 16 lanes each, the loads of all of a lane's units in flight
+  constexpr int UK = kChunk * 16 / 256;
+  if (parts & kPartK) {
+    int64_t slot[UK];
+    uint4 kv[UK];
+#pragma unroll
+    for (int k = 0; k < UK; ++k) {
+      const int i = min((tid >> 4) + 16 * k, cnt - 1);   // past the end: not stored
+      slot[k] = p.slot_mapping[tok0 + i];
+      kv[k] = reinterpret_cast<const uint4*>(p.k + ((tok0 + i) * p.h_kv + hk) * kD)[tid & 15];
+    }
+#pragma unroll
+    for (int k = 0; k < UK; ++k) {
+      const int i = (tid >> 4) + 16 * k, c8 = tid & 15;
+      if (i >= cnt) continue;
+      const int64_t crow = ((slot[k] / kPage) * p.h_kv + hk) * kPage + slot[k] % kPage;
+      float xc[8];
+      center8(kv[k], *reinterpret_cast<const uint4*>(sm.mean + grp * kMeanStride + c8 * 16), xc);
+      if (p.smooth) {
+        float* dst = sm.kc + i * kKcStride + c8 * 8;
+        *reinterpret_cast<float4*>(dst) = make_float4(xc[0], xc[1], xc[2], xc[3]);
+        *reinterpret_cast<float4*>(dst + 4) = make_float4(xc[4], xc[5], xc[6], xc[7]);
+      }
+      uint32_t sc;
+      const uint32_t w = encode_lane<MX>(xc, MX ? 1.0f : sm.ts[grp], sm.rcp_sd, &sc);
+      *reinterpret_cast<uint32_t*>(p.k_codes + crow * 64 + c8 * 4) = w;
+      if (c8 % L == 0) {
+        p.k_scales[crow * 8 + c8 / L] = (uint8_t)sc;
+        if (MX) p.k_scales[crow * 8 + 4 + c8 / L] = 0;
+      }
+    }
+  }
+  __syncthreads();   // the centered rows
+
+  // Q rows: 16 lanes each
+  const int nun = (parts & kPartQ) ? cnt * grp * 16 : 0;   // a multiple of 16: the lanes of a group act together
+  for (int u0 = tid; u0 < nun; u0 += 256 * U) {
+    uint4 v[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int r = min(u0 + 256 * k, nun - 1) >> 4;   // past the end: not stored
+      v[k] = reinterpret_cast<const uint4*>(p.q + ((tok0 + r / grp) * p.h_q + hk * grp + r % grp) * kD)[u0 & 15];
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const int u = u0 + 256 * k;
+      if (u < nun) {
+        const int r = u >> 4, c8 = u & 15, j = r % grp;
+        const int64_t row = (tok0 + r / grp) * p.h_q + hk * grp + j;
+        float xc[8];
+        center8(v[k], *reinterpret_cast<const uint4*>(sm.mean + j * kMeanStride + c8 * 16), xc);
+        uint32_t sc;
+        const uint32_t w = encode_lane<MX>(xc, MX ? 1.0f : sm.ts[j], sm.rcp_sd, &sc);
+        *reinterpret_cast<uint32_t*>(p.q_codes + row * 64 + c8 * 4) = w;
+        if (c8 % L == 0) {
+          p.q_scales[row * 8 + c8 / L] = (uint8_t)sc;
+          if (MX) p.q_scales[row * 8 + 4 + c8 / L] = 0;
+        }
+      }
+    }
+  }
+
+  // Delta_S: one lane per (token, query head), lanes on consecutive tokens; the
+  // last lanes first, so that a few chains do not follow the waves' Q rows
+  if (p.smooth && (parts & kPartK)) {
+    for (int u = 255 - tid; u < cnt * grp; u += 256) {
+      const int i = u % cnt, j = u / cnt;
+      const float* x = sm.kc + i * kKcStride;
+      const uint8_t* qm = sm.mean + j * kMeanStride;
+      float d = 0.0f;
+#pragma unroll 4
+      for (int w = 0; w < 16; ++w) {
+        const uint4 qv = *reinterpret_cast<const uint4*>(qm + 16 * w);
+        const float4 x0 = *reinterpret_cast<const float4*>(x + 8 * w), x1 = *reinterpret_cast<const float4*>(x + 8 * w + 4);
+        const uint32_t q4[4] = {qv.x, qv.y, qv.z, qv.w};
+        const float xv[8] = {x0.x, x0.y, x0.z, x0.w, x1.x, x1.y, x1.z, x1.w};
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          d = __builtin_fmaf(__uint_as_float((e & 1) == 0 ? (q4[e >> 1] << 16) : (q4[e >> 1] & 0xFFFF0000u)), xv[e], d);
+      }
+      const int64_t slot = p.slot_mapping[tok0 + i];
+      p.ds[((slot / kPage) * p.h_q + hk * grp + j) * kPage + slot % kPage] = bf16_rne(d);
+    }
+  }
+
+  // V: whole channel rows where the chunk is one page, else a byte per (token, channel)
+  if (!(parts & kPartV)) return;
+  const bool page_run = sm.page_start && cnt == kChunk;
+  if (page_run || (p.pv == 2 && sm.page_start))
+    quant_v_part(p, tok0, cnt, p.slot_mapping[tok0] / kPage, hk, tid & 63, (tid >> 6) * 16, page_run, sm.rcp_sd);
+  if (!page_run) {
+    for (int u = tid; u < cnt * kD; u += 256) {
+      const int c = u % kD, i = u / kD;
+      const int64_t slot = p.slot_mapping[tok0 + i];
+      const uint16_t vb = p.v[((tok0 + i) * p.h_kv + hk) * kD + c];
+      const int64_t at = (((slot / kPage) * p.h_kv + hk) * kD + c) * kPage + slot % kPage;
+      p.v_codes[at] = (uint8_t)e4m3_rne_sat(bf16_to_f32(vb));
+      if (p.pv == 1) reinterpret_cast<uint16_t*>(p.v_aux)[at] = vb;
+    }
+  }
+}
+
+// sm.rcp_sd and, for cnt >= 1 tokens from tok0, sm.page_start (no barrier)
+__device__ __forceinline__ void group_tables(const QuantParams& p, GroupSmem& sm, int64_t tok0, int cnt) {
+  const int tid = threadIdx.x;
+  if (tid < 64 && cnt > 0) {
+    const int64_t s0 = p.slot_mapping[tok0];
+    const bool ok = (s0 % kPage == 0) && (tid >= cnt || p.slot_mapping[tok0 + tid] == s0 + tid);
+    const bool all = __builtin_amdgcn_ballot_w64(!ok) == 0;
+    if (tid == 0) sm.page_start = all ? 1 : 0;
+  }
+  if (tid >= 128) sm.rcp_sd[tid - 128] = (tid & 0x7F) && (tid & 0x7F) < 0x7F ? __fdiv_rn(1.0f, e4m3_value(tid & 0x7F)) : 0.0f;
+}
+
+template <bool MX>
+__global__ __launch_bounds__(256) void quantize_group_kernel(QuantParams p) {
+  __shared__ GroupSmem sm;
+  const int b = blockIdx.z, tid = threadIdx.x;
+  const int hk = blockIdx.y % p.h_kv;
+  const int parts = (int)gridDim.y == p.h_kv ? kPartAll : 1 << (blockIdx.y / p.h_kv);   // 1 or 3 workgroups a group
+  const int64_t t0 = p.cu_seqlens[b];
+  const int n = p.cu_seqlens[b + 1] - (int)t0;
+  const int i0 = blockIdx.x * kChunk;
+  if (i0 >= n) return;
+  const int cnt = min(kChunk, n - i0), grp = p.h_q / p.h_kv;
+  group_tables(p, sm, t0 + i0, cnt);
+  for (int u = tid; u < (grp + 1) * (kD / 8); u += 256) {
+    const int j = u / (kD / 8), w = u % (kD / 8);
+    uint4 m = make_uint4(0, 0, 0, 0);
+    if (p.smooth) m = reinterpret_cast<const uint4*>(mean_row(p, b, j < grp ? hk * grp + j : p.h_q + hk))[w];
+    *reinterpret_cast<uint4*>(sm.mean + j * kMeanStride + w * 16) = m;
+  }
+  if (tid <= grp) sm.ts[tid] = tid < grp ? p.q_tscale[b * p.h_q + hk * grp + tid] : p.k_tscale[b * p.h_kv + hk];
+  __syncthreads();
+  quant_group<MX>(p, sm, t0 + i0, cnt, hk, parts);
+}
+
+// The whole pass in one launch for calls whose sequences have at most 64 tokens
+// (a decode step's cache write, a short prompt): the statistics of a head group
+// need the group's tokens only, and one chunk holds them all.  The sums run
+// over the tokens in order, as in stats_partial_kernel.
+template <bool MX>
+__global__ __launch_bounds__(256) void quantize_short_kernel(QuantParams p) {
+  __shared__ GroupSmem sm;
+  // one workgroup for all parts (grid z = 1) or one each (3); the Q part, or the
+  // only workgroup, writes the Q statistics, the K part those of K
+  const int hk = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
+  const int parts = gridDim.z == 1 ? kPartAll : 1 << blockIdx.z;
+  const int64_t t0 = p.cu_seqlens[b];
+  const int n = min(p.cu_seqlens[b + 1] - (int)t0, kChunk);   // at most max_seqlen by contract
+  const int grp = p.h_q / p.h_kv;
+  const bool want_sum = p.compute_stats && p.smooth;
+  group_tables(p, sm, t0, n);
+  // 16 lanes per head row (the group's Q heads, then K), 8 channels per lane
+  for (int u0 = 0; u0 < (grp + 1) * 16; u0 += 256) {
+    const int u = u0 + tid, j = u >> 4, oct = u & 15;
+    const bool act = j <= grp, isq = j < grp;
+    const int hh = isq ? hk * grp + j : p.h_q + hk;
+    float sum[8], mx[8], mn[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      sum[e] = 0.0f;
+      mx[e] = -INFINITY;
+      mn[e] = INFINITY;
+    }
+    // the V part needs no statistics; the K part those of Q only for their means
+    const bool want = parts == kPartAll || parts == kPartQ || (parts == kPartK && (want_sum || !isq));
+    const bool own = parts & (isq ? kPartQ : kPartK);
+    if (act && want && p.need_partials && (isq || p.stats_k)) {
+      const int H = isq ? p.h_q : p.h_kv;
+      const uint4* src = reinterpret_cast<const uint4*>((isq ? p.q : p.k) + (t0 * H + (isq ? hh : hk)) * kD) + oct;
+      for (int t = 0; t < n; t += 8) {
+        uint4 w[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) w[k] = src[(int64_t)min(t + k, n - 1) * H * (kD / 8)];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+          if (t + k < n) {
+            const uint32_t wd[4] = {w[k].x, w[k].y, w[k].z, w[k].w};
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+              const float x = __uint_as_float((e & 1) ? (wd[e >> 1] & 0xFFFF0000u) : (wd[e >> 1] << 16));
+              sum[e] += x;
+              mx[e] = fmaxf(mx[e], x);
+              mn[e] = fminf(mn[e], x);
+            }
+          }
+        }
+      }
+    }
+    float amax = 0.0f;
+    if (act) {
+      uint16_t* mrow = mean_row(p, b, hh) + oct * 8;
+      uint32_t mw[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        uint16_t m = 0;
+        if (want_sum && n > 0) m = bf16_rne(__fdiv_rn(sum[e], (float)n));
+        else if (!p.compute_stats && p.smooth) m = mrow[e];
+        if (p.compute_stats && own) mrow[e] = m;
+        mw[e >> 1] |= (uint32_t)m << (16 * (e & 1));
+        if (p.need_partials && want && n > 0) {
+          const float mu = bf16_to_f32(m);
+          amax = fmaxf(amax, fmaxf(__builtin_fabsf(mx[e] - mu), __builtin_fabsf(mn[e] - mu)));
+        }
+      }
+      *reinterpret_cast<uint4*>(sm.mean + j * kMeanStride + oct * 16) = make_uint4(mw[0], mw[1], mw[2], mw[3]);
+    }
+    for (int off = 1; off < 16; off <<= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
+    if (act && oct == 0) {
+      float ts;
+      if (!isq && !p.stats_k) {
+        ts = p.k_tscale[b * p.h_kv + hk];   // frozen
+      } else {
+        ts = (p.tscale_unit || p.mx) ? 1.0f : tensor_scale(amax);
+        if (own) write_tscale(p, b, hh, amax);
+      }
+      sm.ts[j] = ts;
+    }
+  }
+  __syncthreads();
+  if (n > 0) quant_group<MX>(p, sm, t0, n, hk, parts);
+}
+
 __global__ void convert_kernel(int fmt, const float* x, int64_t n, uint8_t* out) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -692,21 +1135,66 @@ __global__ void convert_kernel(int fmt, const float* x, int64_t n, uint8_t* out)
   out[i] = (uint8_t)c;
 }
 
+// Where the launch shapes change (all give the same bytes; times of the whole
+// call on one MI355X, 32:8 heads unless noted):
+//  - at most 64 tokens per sequence: one launch (32 x 1 token 52 -> 9.2 us, 8 x
+//    64 tokens of 40:8 131 -> 23.6 us);
+//  - statistics by one wave per (head, block) up to kWaveStats waves, about 18
+//    per SIMD: 4048 tokens in four prompts 213 -> 154 us, 32768 tokens 40:8 (12K
+//    waves) 265 -> 254 us, 65536 tokens 8:2 (5K) 137 -> 100 us; at 65536 tokens
+//    40:8 (25K) the 256-thread shape is the better one, 452 against 463 us;
+//  - the short finish up to kShortBlocks blocks of the longest sequence: 16 x
+//    2000 tokens 303 -> 240 us; 64 blocks 63.9 -> 62.6 us; 128 blocks 102.2
+//    against 104.8 us;
+//  - quantization by KV head group up to kGroupChunks chunks: 4096 tokens 40:8
+//    171 -> 94 us, 16 x 2000 tokens (516 chunks) 303 -> 280 us, 32768 tokens
+//    40:8 (513) 254 -> 250 us; 65536 tokens 40:8 (1025) 463 against 499 us;
+//  - a workgroup per part up to kPartGroups head groups, about two per CU: 65
+//    tokens 24.8 -> 19.2 us, 777 tokens 23.8 -> 20.4 us; 16 x 2000 tokens (4128
+//    groups) 206 us in one part against 215 us.
+constexpr int64_t kWaveStats = 18432, kGroupChunks = 520, kPartGroups = 512;
+constexpr int kOnePartTokens = 8;   // so few tokens that the parts cost more than they overlap
+
 hipError_t launch_quantize(const QuantParams& p, hipStream_t stream) {
   const int hs = p.h_q + (p.stats_k ? p.h_kv : 0);
+  const bool group_ok = p.h_q / p.h_kv <= kMaxGroupLds;
+  if (p.max_seqlen <= kChunk && group_ok) {
+    const bool split = p.max_seqlen > kOnePartTokens && (int64_t)p.batch * p.h_kv <= kPartGroups;
+    const dim3 grid(p.h_kv, p.batch, split ? 3 : 1);
+    if (p.mx) quantize_short_kernel<true><<<grid, dim3(256), 0, stream>>>(p);
+    else quantize_short_kernel<false><<<grid, dim3(256), 0, stream>>>(p);
+    return hipGetLastError();
+  }
+  // chunks and blocks of the call, at most (the sequence lengths are on the device)
+  const int64_t blocks = (int64_t)p.total_tokens / 128 + p.batch;
+  const int64_t chunks = (int64_t)p.total_tokens / kChunk + p.batch;
   if (p.need_partials && p.max_seqlen > 0) {
-    stats_partial_kernel<<<dim3((p.max_seqlen + 127) / 128, p.batch), dim3(256), 0, stream>>>(p);
+    const unsigned nb = (p.max_seqlen + 127) / 128;
+    if (blocks * hs <= kWaveStats && p.max_seqlen <= 128 * 65535)
+      stats_partial_wave_kernel<<<dim3(hs, nb, p.batch), dim3(64), 0, stream>>>(p);
+    else
+      stats_partial_kernel<<<dim3(nb, p.batch), dim3(256), 0, stream>>>(p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
-  stats_final_kernel<<<dim3(hs * 4, p.batch), dim3(kFinThreads), 0, stream>>>(p);
+  if (p.max_seqlen <= kShortBlocks * 128)
+    stats_final_short_kernel<<<dim3(hs, p.batch), dim3(kD), 0, stream>>>(p);
+  else
+    stats_final_kernel<<<dim3(hs * 4, p.batch), dim3(kFinThreads), 0, stream>>>(p);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   if (p.total_tokens > 0 && p.max_seqlen > 0) {
-    const dim3 grid((p.max_seqlen + kChunk - 1) / kChunk, p.batch);
-    const size_t lds = (size_t)(p.h_q + p.h_kv) * (kMeanStride + sizeof(float));
-    if (p.mx) quantize_kernel<true><<<grid, dim3(256), lds, stream>>>(p);
-    else quantize_kernel<false><<<grid, dim3(256), lds, stream>>>(p);
+    const unsigned nc = (p.max_seqlen + kChunk - 1) / kChunk;
+    if (group_ok && chunks <= kGroupChunks) {
+      const dim3 grid(nc, p.h_kv * (chunks * p.h_kv <= kPartGroups ? 3 : 1), p.batch);
+      if (p.mx) quantize_group_kernel<true><<<grid, dim3(256), 0, stream>>>(p);
+      else quantize_group_kernel<false><<<grid, dim3(256), 0, stream>>>(p);
+    } else {
+      const dim3 grid(nc, p.batch);
+      const size_t lds = (size_t)(p.h_q + p.h_kv) * (kMeanStride + sizeof(float));
+      if (p.mx) quantize_kernel<true><<<grid, dim3(256), lds, stream>>>(p);
+      else quantize_kernel<false><<<grid, dim3(256), lds, stream>>>(p);
+    }
     e = hipGetLastError();
   }
   return e;
