@@ -105,19 +105,120 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void decode_kernel(DecodePa
   decode_partition<SMOOTH, MX, false>(p, b, hk, grp * kWavesPerBlock + wave, nullptr);
 }
 
-// One wave per (sequence, query head).  A separate launch: merging in the
-// last-arriving decode wave needs the partition states made visible across
-// the XCDs' L2 caches (an L2 write-back per wave, or write-through stores and
-// an arrival counter), which measured slower than this second launch.
-__global__ __launch_bounds__(64) void merge_kernel(DecodeParams p) {
+// Merge of the partition states, one workgroup per (query head, sequence).  A
+// separate launch: merging in the last-arriving decode wave needs the partition
+// states made visible across the XCDs' L2 caches (an L2 write-back per wave, or
+// write-through stores and an arrival counter), which measured slower than this
+// second launch.  The states are read once, a chunk's 32 rows in flight per
+// wave; what it costs is the round trips, so past one chunk eight waves share
+// the chunks, a round of eight at a time (one sequence of 131072 keys, 512
+// partitions, 40 heads: 75 -> 10 us; 17 partitions 5.6 -> 3.5 us).
+template <int WAVES, int N>
+__global__ __launch_bounds__(WAVES * 64) void merge_kernel(DecodeParams p) {
   const int h = blockIdx.x, b = blockIdx.y;
-  merge_head(p, b, h, (p.kv_len[b] + p.partition_tokens - 1) / p.partition_tokens);
+  const int np = (p.kv_len[b] + p.partition_tokens - 1) / p.partition_tokens;
+  if (WAVES == 1) {
+    merge_head<N>(p, b, h, np);
+    return;
+  }
+  __shared__ float wave_top[WAVES];
+  __shared__ float2 part_o[WAVES][64];
+  __shared__ float part_l[WAVES];
+  const float* st = head_states(p, b, h);
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  float2 o[N];
+  if (wave * kMergeChunk < np) merge_load(st, wave * kMergeChunk, np, o);
+  float M = -INFINITY;
+  for (int q = threadIdx.x; q < np; q += WAVES * 64) M = fmaxf(M, st[(int64_t)q * (kD + 2)]);
+  M = wave_max64(M);
+  if (lane == 0) wave_top[wave] = M;
+  __syncthreads();
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) M = fmaxf(M, wave_top[w]);
+  float L = 0.0f, O0 = 0.0f, O1 = 0.0f;   // wave 0
+  for (int r0 = 0; r0 < np; r0 += WAVES * kMergeChunk) {
+    const int q0 = r0 + wave * kMergeChunk;
+    if (q0 < np) {
+      if (r0 > 0) merge_load(st, q0, np, o);
+      const MergeSum c = merge_chunk(o, merge_ml(st, q0, np), q0, np, M);
+      part_o[wave][lane] = make_float2(c.o0, c.o1);
+      if (lane == 0) part_l[wave] = c.l;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      for (int w = 0; w < WAVES && r0 + w * kMergeChunk < np; ++w) {
+        L += part_l[w];
+        O0 += part_o[w][lane].x;
+        O1 += part_o[w][lane].y;
+      }
+    }
+    __syncthreads();
+  }
+  if (wave == 0) merge_store(p, b, h, L, O0, O1, np > 0);
+}
+
+// Short contexts: one workgroup per (KV head, sequence) whose waves are its
+// partitions; the states stay in LDS and wave j merges query heads j, j + WAVES,
+// ... after a barrier.  Saves the merge launch and its round trips to memory
+// (group_decode says when).
+template <bool SMOOTH, bool MX, int WAVES>
+__global__ __launch_bounds__(WAVES * 64, 1) void decode_group_kernel(DecodeParams p) {
+  extern __shared__ __attribute__((aligned(16))) float states[];   // [WAVES][grp][kD + 2]
+  const int hk = blockIdx.x, b = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int grp = p.h_q / p.h_kv, slice = grp * (kD + 2);
+  decode_partition<SMOOTH, MX, false, true>(p, b, hk, wave, nullptr, states + wave * slice);
+  __syncthreads();
+  const int np = (p.kv_len[b] + p.partition_tokens - 1) / p.partition_tokens;
+  for (int j = wave; j < grp; j += WAVES) {
+    const float* st = states + j * (kD + 2);
+    float M = -INFINITY, L = 0.0f, O0 = 0.0f, O1 = 0.0f;
+    for (int q = 0; q < np; ++q) M = fmaxf(M, st[q * slice]);
+    for (int q = 0; q < np; ++q) {
+      const float* sq = st + q * slice;
+      const float f = __builtin_amdgcn_exp2f(sq[0] - M);
+      L = __builtin_fmaf(f, sq[1], L);
+      O0 = __builtin_fmaf(f, sq[2 + 2 * lane], O0);
+      O1 = __builtin_fmaf(f, sq[3 + 2 * lane], O1);
+    }
+    merge_store(p, b, hk * grp + j, L, O0, O1, np > 0);
+  }
+}
+
+template <bool SMOOTH, bool MX>
+hipError_t launch_decode_group(const DecodeParams& p, hipStream_t stream) {
+  const dim3 grid(p.h_kv, p.batch);
+  const size_t slice = (size_t)(p.h_q / p.h_kv) * (kD + 2) * sizeof(float);
+  if (p.max_partitions <= 1) decode_group_kernel<SMOOTH, MX, 1><<<grid, dim3(64), slice, stream>>>(p);
+  else if (p.max_partitions <= 2) decode_group_kernel<SMOOTH, MX, 2><<<grid, dim3(128), 2 * slice, stream>>>(p);
+  else if (p.max_partitions <= 4) decode_group_kernel<SMOOTH, MX, 4><<<grid, dim3(256), 4 * slice, stream>>>(p);
+  else decode_group_kernel<SMOOTH, MX, 8><<<grid, dim3(512), 8 * slice, stream>>>(p);
+  return hipGetLastError();
+}
+
+// When a call takes decode_group_kernel (times of the whole call, 32:8 heads; the
+// two launches / one): up to 4 partitions while there are at most kGroupMaxWaves
+// waves, two per SIMD of the chip: 1 x 60 keys 12.0 / 9.0 us, 900 keys x 16 14.0
+// / 10.0, 500 x 256 (4096 waves) 50.1 / 44.1.  5 to 8 partitions only when the
+// packed grid's workgroups would share compute units anyway (more than 256 of
+// them): 1500 keys x 32 22.1 / 17.3 us, x 64 35.9 / 32.9, but x 8 13.1 / 14.4 (a
+// unit then has eight waves' keys to fetch where two workgroups had two).
+constexpr int kGroupWaves = 8, kGroupMaxWaves = 4096;
+
+bool group_decode(const DecodeParams& p) {
+  if (p.max_partitions > kGroupWaves) return false;
+  const int w = p.max_partitions <= 2 ? p.max_partitions : (p.max_partitions <= 4 ? 4 : kGroupWaves);
+  if ((int64_t)p.batch * p.h_kv * w > kGroupMaxWaves) return false;
+  return w <= 4 || (int64_t)p.batch * 2 * ((p.h_kv + 7) / 8 * 8) > 256;
 }
 
 }  // namespace
 
 hipError_t launch_decode(const DecodeParams& p, hipStream_t stream) {
   if (p.batch == 0) return hipSuccess;
+  if (group_decode(p)) {
+    if (p.mx) return p.smooth ? launch_decode_group<true, true>(p, stream) : launch_decode_group<false, true>(p, stream);
+    return p.smooth ? launch_decode_group<true, false>(p, stream) : launch_decode_group<false, false>(p, stream);
+  }
   const int groups = (p.max_partitions + kWavesPerBlock - 1) / kWavesPerBlock;
   const dim3 block(kWavesPerBlock * 64);
   if (p.batch <= kDecodePackedMaxBatch) {
@@ -142,7 +243,10 @@ hipError_t launch_decode(const DecodeParams& p, hipStream_t stream) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  merge_kernel<<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
+  if (p.max_partitions <= 8) merge_kernel<1, 8><<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
+  else if (p.max_partitions <= 16) merge_kernel<1, 16><<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
+  else if (p.max_partitions <= kMergeChunk) merge_kernel<1, kMergeChunk><<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
+  else merge_kernel<8, kMergeChunk><<<dim3(p.h_q, p.batch), dim3(512), 0, stream>>>(p);
   return hipGetLastError();
 }
 

@@ -20,57 +20,99 @@ constexpr int kWavesPerBlock = 4;
 // each wait: PV of tile j+1 waits for V(j+1) with K(j) still in flight, QK of
 // tile j for K(j) with V(j) in flight.
 
-// Merge of the partition states of query head h of sequence b by one wave:
-// lane l owns channels l and l + 64.  Per channel: the maximum of m over the
-// partitions, then L and O accumulated over the partitions in order, O / L
-// rounded to BF16.  The loads of 16 partitions are issued together.
-__device__ __forceinline__ void merge_head(const DecodeParams& p, int b, int h, int np) {
-  constexpr int kBatch = 16;
+// Merge of the partition states of a query head (log-sum-exp): M is the maximum
+// of m over the partitions; L and O are sums over chunks of kMergeChunk
+// partitions, each chunk summed in partition order and the chunk sums added in
+// chunk order, so that the result does not depend on how many waves share the
+// chunks; out = O / L as BF16.  Lane l owns channels 2l and 2l + 1.
+constexpr int kMergeChunk = 32;
+
+struct MergeSum {
+  float l, o0, o1;
+};
+
+__device__ __forceinline__ const float* head_states(const DecodeParams& p, int b, int h) {
+  return p.ws + ((int64_t)b * p.h_q + h) * p.max_partitions * (kD + 2);
+}
+
+// maximum over the lanes of a wave
+__device__ __forceinline__ float wave_max64(float x) {
+  for (int off = 32; off >= 1; off >>= 1) x = fmaxf(x, __shfl_xor(x, off));
+  return x;
+}
+
+// The first N O rows of the chunk at partition q0 (all loads in flight; past np
+// the last partition repeats and is not used).
+template <int N>
+__device__ __forceinline__ void merge_load(const float* st, int q0, int np, float2 (&o)[N]) {
   const int lane = threadIdx.x & 63;
-  const float* st = p.ws + ((int64_t)b * p.h_q + h) * p.max_partitions * (kD + 2);
-  float M = -INFINITY;
-  for (int q0 = 0; q0 < np; q0 += kBatch) {
-    float mv[kBatch];
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) mv[j] = q0 + j < np ? st[(q0 + j) * (kD + 2)] : -INFINITY;
+  for (int j = 0; j < N; ++j)
+    o[j] = *reinterpret_cast<const float2*>(st + (int64_t)min(q0 + j, np - 1) * (kD + 2) + 2 + 2 * lane);
+}
+
+// ml: this lane's partition q0 + lane (m, l), for lanes below kMergeChunk
+template <int N>
+__device__ __forceinline__ MergeSum merge_chunk(const float2 (&o)[N], float2 ml, int q0, int np, float M) {
+  const float f = __builtin_amdgcn_exp2f(ml.x - M);
+  MergeSum c = {0.0f, 0.0f, 0.0f};
 #pragma unroll
-    for (int j = 0; j < kBatch; ++j) M = fmaxf(M, mv[j]);
+  for (int j = 0; j < N; ++j) {
+    if (q0 + j < np) {
+      const float fj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), j));
+      const float lj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ml.y), j));
+      c.l = __builtin_fmaf(fj, lj, c.l);
+      c.o0 = __builtin_fmaf(fj, o[j].x, c.o0);
+      c.o1 = __builtin_fmaf(fj, o[j].y, c.o1);
+    }
   }
+  return c;
+}
+
+__device__ __forceinline__ float2 merge_ml(const float* st, int q0, int np) {
+  const int lane = threadIdx.x & 63;
+  return *reinterpret_cast<const float2*>(st + (int64_t)min(q0 + min(lane, kMergeChunk - 1), np - 1) * (kD + 2));
+}
+
+__device__ __forceinline__ void merge_store(const DecodeParams& p, int b, int h, float L, float O0, float O1, bool any) {
+  const int lane = threadIdx.x & 63;
+  const uint32_t lo = bf16_rne(any ? __fdiv_rn(O0, L) : 0.0f), hi = bf16_rne(any ? __fdiv_rn(O1, L) : 0.0f);
+  *reinterpret_cast<uint32_t*>(p.out + ((int64_t)b * p.h_q + h) * kD + 2 * lane) = lo | (hi << 16);
+}
+
+// The whole merge of one query head by one wave, up to N partitions in flight
+// (N < kMergeChunk: np is at most N).
+template <int N>
+__device__ __forceinline__ void merge_head(const DecodeParams& p, int b, int h, int np) {
+  const float* st = head_states(p, b, h);
   float L = 0.0f, O0 = 0.0f, O1 = 0.0f;
-  for (int q0 = 0; q0 < np; q0 += kBatch) {
-    float mv[kBatch], lv[kBatch], o0[kBatch], o1[kBatch];
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      const bool in = q0 + j < np;
-      const float* sq = st + (q0 + j) * (kD + 2);
-      mv[j] = in ? sq[0] : 0.0f;
-      lv[j] = in ? sq[1] : 0.0f;
-      o0[j] = in ? sq[2 + lane] : 0.0f;
-      o1[j] = in ? sq[2 + 64 + lane] : 0.0f;
-    }
-#pragma unroll
-    for (int j = 0; j < kBatch; ++j) {
-      if (q0 + j < np) {
-        const float f = __builtin_amdgcn_exp2f(mv[j] - M);
-        L = __builtin_fmaf(f, lv[j], L);
-        O0 = __builtin_fmaf(f, o0[j], O0);
-        O1 = __builtin_fmaf(f, o1[j], O1);
-      }
+  if (np > 0) {
+    float2 o[N];
+    merge_load(st, 0, np, o);   // the first chunk's rows, beside the maxima
+    float M = -INFINITY;
+    for (int q = threadIdx.x & 63; q < np; q += 64) M = fmaxf(M, st[(int64_t)q * (kD + 2)]);
+    M = wave_max64(M);
+    for (int q0 = 0; q0 < np; q0 += kMergeChunk) {
+      if (q0 > 0) merge_load(st, q0, np, o);
+      const MergeSum c = merge_chunk(o, merge_ml(st, q0, np), q0, np, M);
+      L += c.l;
+      O0 += c.o0;
+      O1 += c.o1;
     }
   }
-  uint16_t* o = p.out + ((int64_t)b * p.h_q + h) * kD;
-  o[lane] = bf16_rne(np > 0 ? __fdiv_rn(O0, L) : 0.0f);
-  o[64 + lane] = bf16_rne(np > 0 ? __fdiv_rn(O1, L) : 0.0f);
+  merge_store(p, b, h, L, O0, O1, np > 0);
 }
 
 // One decode work item (sequence b, KV head hk, partition part) executed by
 // one wave; it writes the partition state to the workspace.  With FUSED, the
 // wave then counts itself in counters[b * h_kv + hk] (device scope); the wave
 // that completes the last partition of (b, hk) merges the group's query heads,
-// writes the outputs and resets the counter to zero for the next call.
-template <bool SMOOTH, bool MX, bool FUSED>
+// writes the outputs and resets the counter to zero for the next call.  With
+// TO_LDS the state of query head hk * grp + j goes to lds + j * (kD + 2) instead
+// (this partition's slice, the caller's).
+template <bool SMOOTH, bool MX, bool FUSED, bool TO_LDS = false>
 __device__ __forceinline__ void decode_partition(const DecodeParams& p, int b, int hk, int part,
-                                                 uint32_t* counters) {
+                                                 uint32_t* counters, float* lds = nullptr) {
   // the item indices are wave-uniform: in scalar registers, the tile loop and
   // its branches are scalar too
   b = __builtin_amdgcn_readfirstlane(b);
@@ -302,7 +344,7 @@ __device__ __forceinline__ void decode_partition(const DecodeParams& p, int b, i
   // partition state: m in log2 units (m * lambda'), l, O[128]
   const float lt = wave_sum16(l);
   if (qvalid) {
-    float* st = p.ws + (((int64_t)b * p.h_q + h) * p.max_partitions + part) * (kD + 2);
+    float* st = TO_LDS ? lds + lr * (kD + 2) : p.ws + (((int64_t)b * p.h_q + h) * p.max_partitions + part) * (kD + 2);
     if (g == 0) {
       st[0] = m * lam2;
       st[1] = lt;
@@ -320,7 +362,7 @@ __device__ __forceinline__ void decode_partition(const DecodeParams& p, int b, i
     prev = __shfl(prev, 0);
     if (prev == (uint32_t)(np - 1)) {   // last partition of (b, hk): merge its query heads
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // every state counted before is visible
-      for (int j = 0; j < grp; ++j) merge_head(p, b, hk * grp + j, np);
+      for (int j = 0; j < grp; ++j) merge_head<kMergeChunk>(p, b, hk * grp + j, np);
       if (lane == 0) atomicExch(&counters[b * p.h_kv + hk], 0u);
     }
   }
