@@ -20,6 +20,7 @@ static_assert(MPFA_STATIC_SCRATCH_BYTES == mpfa::kStaticScratchBytes,
 namespace {
 
 constexpr int kPrefillRows = 256;   // query rows per prefill workgroup
+constexpr int kFewRows = 32;        // the same for calls with few query rows
 constexpr int kMaxKvHeads = mpfa::kMaxKvHeadsQuant;
 constexpr int kMaxDecodeGroup = 8;  // query heads per KV head packed in one decode wave
 constexpr float kLambda = 0.12751743074173085f;   // log2(e) / sqrt(128)
@@ -118,6 +119,21 @@ mpfa_status check_decode(const mpfa_decode_args* a, hipStream_t s) {
 
 }  // namespace
 
+// Whether a call may gain from 32-row workgroups (prefill_few_block, which decides
+// per sequence): the method's own kernels, at most 8 such blocks per compute
+// unit, and a page table that leaves room for a context long enough to pay (the
+// lengths themselves are on the device).
+static bool prefill_few(const mpfa_prefill_args* a) {
+  if (a->flags & (MPFA_SEED_ELEMWISE | MPFA_PV_BF16 | MPFA_PV_NVFP4)) return false;
+  const int64_t blocks = ((int64_t)a->max_seqlen_q + kFewRows - 1) / kFewRows * a->h_q * a->batch;
+  if (blocks > 8 * mpfa::kComputeUnits) return false;
+  // the least blocks per compute unit: those of the longest sequence alone
+  const int64_t least = blocks / a->batch;
+  const float per_cu = (float)((least + mpfa::kComputeUnits - 1) / mpfa::kComputeUnits);
+  const float most = 0.5f * ((float)a->max_pages + 1.0f);   // tiles
+  return 4.0f + per_cu * (7.5f + 0.3125f * most) < 5.0f + ((a->flags & MPFA_MXFP4) ? 2.0f : 2.65f) * most;
+}
+
 // Host-side validation of the prefill arguments and their launch parameters.
 static mpfa_status prefill_params(const mpfa_prefill_args* a, mpfa::PrefillParams& p) {
   if (!a) return MPFA_ERR_INVALID;
@@ -145,7 +161,12 @@ static mpfa_status prefill_params(const mpfa_prefill_args* a, mpfa::PrefillParam
   p.h_q = a->h_q;
   p.h_kv = a->h_kv;
   p.max_pages = a->max_pages;
-  p.n_qtiles = (int)n_qtiles;
+  // no order to choose when every item is resident at once, nothing to gain over
+  // short contexts (up to 8 tiles)
+  p.order = a->batch > 1 && a->batch <= mpfa::kOrderMaxBatch && a->max_pages > 16 &&
+            n_qtiles * a->h_q * (int64_t)a->batch > mpfa::kComputeUnits;
+  p.few = prefill_few(a);
+  p.n_qtiles = p.few ? (a->max_seqlen_q + kFewRows - 1) / kFewRows : (int)n_qtiles;
   p.smooth = smooth;
   p.seed_mfma = (a->flags & MPFA_SEED_MFMA) != 0;
   p.seed_elem = (a->flags & MPFA_SEED_ELEMWISE) != 0;

@@ -16,8 +16,11 @@
 // (measured slower than two launches).  The host therefore places the decode
 // rounds first: they stream the KV pages at full bandwidth on every unit, then
 // the prefill tiles follow in their largest-first order.
+#include <type_traits>
+
 #include "decode_body.h"
 #include "prefill_body.h"
+#include "prefill_split.h"
 
 namespace mpfa {
 
@@ -30,9 +33,11 @@ namespace {
 // every prefill item on the XCD its index selects (index = block - 8 * decode
 // rounds before it, the same residue mod 8), so the KV-head-per-XCD placement
 // of the prefill items holds as in the separate launch.
-template <bool SMOOTH, bool MX>
+// FEW: the prefill items are those of prefill_few_kernel (the same bytes as the
+// separate calls either way).
+template <bool SMOOTH, bool MX, bool FEW>
 __global__ __launch_bounds__(512, 1) void mixed_kernel(MixedParams m) {
-  __shared__ __attribute__((aligned(16))) PrefillSmemT<MX, kPvFp8> lds;
+  __shared__ __attribute__((aligned(16))) std::conditional_t<FEW, FewSmem<SMOOTH, MX>, PrefillSmemT<MX, kPvFp8>> lds;
   const int i = blockIdx.x, r = i >> 3;
   // decode round k sits at round first + k * stride (k < n_dec_rounds)
   const int rel = r - m.first;
@@ -41,7 +46,8 @@ __global__ __launch_bounds__(512, 1) void mixed_kernel(MixedParams m) {
   if (!is_dec) {
     const int bid = i - 8 * dec_before;
     if (bid >= m.n_pre_blocks) return;
-    prefill_item<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8, 8>(m.pre, bid, lds);
+    if constexpr (FEW) prefill_few_block<SMOOTH, MX>(m.pre, bid, lds);
+    else prefill_block<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8>(m.pre, bid, lds);
     return;
   }
   // decode group (round, lane of the round): wave w takes item 8 * group + w =
@@ -56,6 +62,12 @@ __global__ __launch_bounds__(512, 1) void mixed_kernel(MixedParams m) {
   decode_partition<SMOOTH, MX, true>(p, b, hk, part, m.counters);
 }
 
+template <bool SMOOTH, bool MX>
+void launch_form(const MixedParams& m, dim3 grid, dim3 block, hipStream_t stream) {
+  if (m.pre.few) mixed_kernel<SMOOTH, MX, true><<<grid, block, 0, stream>>>(m);
+  else mixed_kernel<SMOOTH, MX, false><<<grid, block, 0, stream>>>(m);
+}
+
 }  // namespace
 
 hipError_t launch_mixed(const MixedParams& m, hipStream_t stream) {
@@ -63,11 +75,11 @@ hipError_t launch_mixed(const MixedParams& m, hipStream_t stream) {
   if (blocks == 0) return hipSuccess;
   const dim3 grid(blocks), block(512);
   if (m.pre.mx) {
-    if (m.pre.smooth) mixed_kernel<true, true><<<grid, block, 0, stream>>>(m);
-    else mixed_kernel<false, true><<<grid, block, 0, stream>>>(m);
+    if (m.pre.smooth) launch_form<true, true>(m, grid, block, stream);
+    else launch_form<false, true>(m, grid, block, stream);
   } else {
-    if (m.pre.smooth) mixed_kernel<true, false><<<grid, block, 0, stream>>>(m);
-    else mixed_kernel<false, false><<<grid, block, 0, stream>>>(m);
+    if (m.pre.smooth) launch_form<true, false>(m, grid, block, stream);
+    else launch_form<false, false>(m, grid, block, stream);
   }
   return hipGetLastError();
 }

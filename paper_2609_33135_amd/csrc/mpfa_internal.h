@@ -8,6 +8,8 @@
 namespace mpfa {
 
 constexpr int kMaxKvHeadsQuant = 32;
+constexpr int kComputeUnits = 256;
+constexpr int kOrderMaxBatch = 64;   // one lane per sequence
 // decode batches up to this many sequences use the packed, XCD-rotated block
 // map (each workgroup looks its work up with an O(batch) scan); larger ones a
 // three-dimensional grid
@@ -43,7 +45,9 @@ struct QuantParams {
 
 struct PrefillParams {
   int batch, h_q, h_kv, max_pages;
-  int n_qtiles;     // max query tiles of one sequence
+  int n_qtiles;     // max query tiles of one sequence (256 rows, or 32 with split)
+  int order;        // 1: sequences may start apart, dispatch the longest items first
+  int few;          // 1: few row blocks, one workgroup per 32 rows (see prefill_few_block)
   int smooth;
   int seed_mfma;    // 1: compensation formed by the rank-one BF16 MFMA, 0: accumulator input
   int seed_elem;    // 1: compensation added to each score after the QK product

@@ -19,17 +19,24 @@
 // The key order inside a 32-row MFMA block is permuted so that the 32 keys a
 // lane holds for a PV MFMA are contiguous (tile_key).
 #include "prefill_body.h"
+#include "prefill_split.h"
 
 namespace mpfa {
 
 namespace {
 
-constexpr int kWaves = 8, kThreads = kWaves * 64;
+constexpr int kThreads = kItemWaves * 64;
 
 template <int SEED, bool MX, int PV, int ABL = 0>
 __global__ __launch_bounds__(kThreads, 1) void prefill_kernel(PrefillParams p) {
   __shared__ __attribute__((aligned(16))) PrefillSmemT<MX, PV> smem;
-  prefill_item<SEED, MX, PV, kWaves, ABL>(p, blockIdx.x, smem);
+  prefill_block<SEED, MX, PV, ABL>(p, blockIdx.x, smem);
+}
+
+template <bool SMOOTH, bool MX>
+__global__ __launch_bounds__(kThreads, 1) void prefill_few_kernel(PrefillParams p) {
+  __shared__ __attribute__((aligned(16))) FewSmem<SMOOTH, MX> sm;
+  prefill_few_block<SMOOTH, MX>(p, blockIdx.x, sm);
 }
 
 #ifdef MPFA_ABLATION_BUILD
@@ -65,7 +72,15 @@ hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream) {
     return hipGetLastError();
   }
 #endif
-  if (p.pv == kPvBf16) {
+  if (p.few) {
+    if (p.mx) {
+      if (p.smooth) prefill_few_kernel<true, true><<<grid, block, 0, stream>>>(p);
+      else prefill_few_kernel<false, true><<<grid, block, 0, stream>>>(p);
+    } else {
+      if (p.smooth) prefill_few_kernel<true, false><<<grid, block, 0, stream>>>(p);
+      else prefill_few_kernel<false, false><<<grid, block, 0, stream>>>(p);
+    }
+  } else if (p.pv == kPvBf16) {
     if (!p.smooth) prefill_kernel<kSeedNone, false, kPvBf16><<<grid, block, 0, stream>>>(p);
     else prefill_kernel<kSeedInit, false, kPvBf16><<<grid, block, 0, stream>>>(p);
   } else if (p.pv == kPvNvfp4) {

@@ -9,6 +9,8 @@ namespace mpfa {
 namespace {
 
 constexpr int kWaveRows = 32;                // query rows per wave: the columns of one 32x32 MFMA
+constexpr int kItemWaves = 8;
+constexpr int kItemRows = kItemWaves * kWaveRows;
 
 // Precision of the PV product: the method's FP8 (P * 448 and V in E4M3), or
 // the two other assignments compared in Sec. 3.1 / Fig. 3a, BF16 P and V, and
@@ -83,11 +85,14 @@ struct VRegs {
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t page_rsrc(const void* base, int bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, bytes, 0x00027000);
 }
-__device__ __forceinline__ u32x4 page_load16(const void* base, int bytes, uint32_t off) {
-  return __builtin_amdgcn_raw_buffer_load_b128(page_rsrc(base, bytes), off, 0, 0);
+__device__ __forceinline__ u32x4 page_load16(const void* base, int bytes, uint32_t off, int scalar_off = 0) {
+  return __builtin_amdgcn_raw_buffer_load_b128(page_rsrc(base, bytes), off, scalar_off, 0);
 }
-__device__ __forceinline__ uint32_t page_load2(const void* base, int bytes, uint32_t off) {
-  return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(page_rsrc(base, bytes), off, 0, 0);
+__device__ __forceinline__ uint32_t page_load4(const void* base, int bytes, uint32_t off, int scalar_off = 0) {
+  return __builtin_amdgcn_raw_buffer_load_b32(page_rsrc(base, bytes), off, scalar_off, 0);
+}
+__device__ __forceinline__ uint32_t page_load2(const void* base, int bytes, uint32_t off, int scalar_off = 0) {
+  return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(page_rsrc(base, bytes), off, scalar_off, 0);
 }
 __device__ __forceinline__ uint32_t page_load1(const void* base, int bytes, uint32_t off) {
   return (uint8_t)__builtin_amdgcn_raw_buffer_load_b8(page_rsrc(base, bytes), off, 0, 0);
@@ -193,19 +198,14 @@ struct ItemState {
   bool wave_active;
   float lam2, seed_scale;
   int pos;             // absolute position of the lane's query
-  f16x8 qop[8];        // NVFP4: exact FP16 query operands (channels 16ks + 8hf .. +7), tensor scale factored out
+  f16x8 qop[8];        // NVFP4: exact FP16 query operands, tensor scale factored out
   u32x4 qraw[2];       // MXFP4: raw codes of channels 64i + 32hf .. +31
   int qscale[2];       // MXFP4: their E8M0 scales
   bf16x8 bseed;        // B operand of the rank-one seed MFMA: 1 in slot 0 of lanes 0..31
 };
 
-// Decode work item `bid` (largest query tiles first, longest-processing-time
-// order) and load the wave's query operands.  Returns false when the item has
-// no rows.
-template <bool MX, int WAVES>
-__device__ __forceinline__ bool item_setup(const PrefillParams& p, int bid, ItemState& st) {
-  constexpr int kRows = WAVES * kWaveRows;
-  int b, h, rank;
+// Sequence, query head and row-tile rank of dispatch position `bid`.
+__device__ __forceinline__ void map_item(const PrefillParams& p, int bid, int& b, int& h, int& rank) {
   if (p.xcd_remap) {
     // block ids are dealt round-robin to the 8 XCDs; give each XCD the query
     // heads of a fixed subset of KV heads so their K/V tiles share its L2.
@@ -225,11 +225,72 @@ __device__ __forceinline__ bool item_setup(const PrefillParams& p, int bid, Item
     h = rem % p.h_q;
     b = rem / p.h_q;
   }
-  const int qtile = p.n_qtiles - 1 - rank;
+}
+
+// Sum over the wave (DPP, no LDS round trips), in every lane.
+__device__ __forceinline__ int wave_sum_all(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);   // row_shr 1, 2, 4, 8
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);  // row_bcast 15
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);  // row_bcast 31
+  return __builtin_amdgcn_readlane(x, 63);
+}
+
+// Dispatch order of a batch whose sequences start at different positions (chunks
+// behind prefixes): position pos is the pos-th longest row tile of the batch, by
+// KV tiles to visit, found by a binary search over the tile count; lanes hold
+// the sequences.  By row-tile index alone a short chunk behind a long prefix,
+// the longest items of all, starts last (chunks of 512, 2048, 1000 rows behind
+// 30000, 5001, 12345 tokens, 32:8: 821 -> 670 us).  Sequences that start
+// together are in that order already.  Returns false past the last item.
+__device__ __forceinline__ bool longest_item(const PrefillParams& p, int pos, int& b, int& tile) {
+  const int lane = threadIdx.x & 63;
+  int qs = 0, nq = 0;
+  if (lane < p.batch) {
+    qs = p.q_start[lane];
+    nq = p.cu_seqlens_q[lane + 1] - p.cu_seqlens_q[lane];
+  }
+  const int items = (nq + kItemRows - 1) / kItemRows;
+  if (pos >= wave_sum_all(items)) return false;
+  // first item of the lane's sequence that visits at least c + 1 tiles (its last tile is >= c)
+  auto first = [&](int c) { const int x = c * kTile - qs; return nq - 1 < x ? items : (x > 0 ? x / kItemRows : 0); };
+  int lo = 0, hi = p.max_pages / 2 + 1;   // the pos-th longest item's last tile is in [lo, hi)
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (wave_sum_all(items - first(mid)) > pos) lo = mid;
+    else hi = mid;
+  }
+  const int f0 = first(lo), f1 = first(lo + 1);
+  const int rest = pos - wave_sum_all(items - f1);   // among the items whose last tile is lo
+  int incl = f1 - f0;
+  for (int d = 1; d < kOrderMaxBatch; d <<= 1) {
+    const int up = __shfl_up(incl, d);
+    if (lane >= d) incl += up;
+  }
+  const uint64_t past = __ballot(incl > rest);
+  b = __ffsll((unsigned long long)past) - 1;
+  tile = __builtin_amdgcn_readlane(f0, b) + rest - (__builtin_amdgcn_readlane(incl, b) - __builtin_amdgcn_readlane(f1 - f0, b));
+  return true;
+}
+
+// Whether the sequences' first positions differ by more than a row tile.
+__device__ __forceinline__ bool starts_differ(const PrefillParams& p) {
+  if (!p.order) return false;
+  const int lane = threadIdx.x & 63;
+  const int x = p.q_start[min(lane, p.batch - 1)], x0 = __builtin_amdgcn_readfirstlane(x);
+  return __ballot(abs(x - x0) > kItemRows) != 0;
+}
+
+// Work item of query head h, rows r0 .. of sequence b (r0 below its row count);
+// loads the wave's query operands.  SPLIT: the item is 32 rows shared by all
+// waves (prefill_split_item), else each wave has 32 rows of its own.
+template <bool MX, int WAVES, bool SPLIT = false>
+__device__ __forceinline__ void item_setup(const PrefillParams& p, int b, int h, int r0, ItemState& st) {
+  constexpr int kRows = SPLIT ? kWaveRows : WAVES * kWaveRows;
   const int q0 = p.cu_seqlens_q[b];
   const int nq = p.cu_seqlens_q[b + 1] - q0;
-  const int r0 = qtile * kRows;
-  if (r0 >= nq) return false;
 
   st.b = b;
   st.h = h;
@@ -250,7 +311,7 @@ __device__ __forceinline__ bool item_setup(const PrefillParams& p, int bid, Item
   st.lam2 = __builtin_ldexpf(p.lam, eqk);        // lambda * tQ * tK
   st.seed_scale = __builtin_ldexpf(1.0f, -eqk);  // Delta_S in accumulator units
 
-  st.wrow0 = r0 + st.wave * kWaveRows;
+  st.wrow0 = r0 + (SPLIT ? 0 : st.wave * kWaveRows);
   st.wave_active = st.wrow0 < nq;
   st.wpos_min = st.qs + st.wrow0;
   st.wpos_max = st.qs + min(st.wrow0 + kWaveRows, nq) - 1;
@@ -271,16 +332,20 @@ __device__ __forceinline__ bool item_setup(const PrefillParams& p, int bid, Item
       st.qscale[i] = valid ? qsc[2 * i + st.hf] : 127;
     }
   } else {
+    // the lane's channels: 16ks + 8hf .. +7 (group ks), or 64hf + 8ks .. +7 (group
+    // 4hf + ks/2; contiguous code bytes); scale times code is exact in FP16
+    const uint2 sw = valid ? *reinterpret_cast<const uint2*>(qsc) : make_uint2(0u, 0u);
+    const uint32_t lo = SPLIT && st.hf ? sw.y : sw.x, hi = sw.y;
+    const f16x2 a = e4m3_pair_f16(lo), b2 = e4m3_pair_f16(lo >> 16), c = e4m3_pair_f16(hi), d = e4m3_pair_f16(hi >> 16);
+    const _Float16 g[8] = {a[0], a[1], b2[0], b2[1], c[0], c[1], d[0], d[1]};
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      const uint32_t cw = valid ? *reinterpret_cast<const uint32_t*>(qc + 8 * ks + 4 * st.hf) : 0u;
-      const uint32_t sc = valid ? qsc[ks] : 0u;
-      st.qop[ks] = dequant8(cw, split_e4m3(sc));
+      const uint32_t cw = valid ? *reinterpret_cast<const uint32_t*>(qc + (SPLIT ? 32 * st.hf + 4 * ks : 8 * ks + 4 * st.hf)) : 0u;
+      st.qop[ks] = dequant8h(cw, g[SPLIT ? ks >> 1 : ks]);
     }
   }
   st.bseed = (bf16x8){};
   if (st.lane < 32) st.bseed[0] = (__bf16)1.0f;
-  return true;
 }
 
 // S^T = seed + K Q^T of one 32-key block (Algorithm 1, scores).
@@ -522,9 +587,8 @@ __device__ __forceinline__ void store_output(const PrefillParams& p, const ItemS
   }
 }
 
-// One prefill work item (query head, 32 * WAVES query rows) executed by a whole
-// workgroup of 64 * WAVES threads; `bid` is the item's position in the dispatch
-// order (largest tiles first).
+// One prefill work item (query head h, query rows r0 .. r0 + 32 * WAVES - 1 of
+// sequence b) executed by a whole workgroup of 64 * WAVES threads.
 //
 // What bounds it: the matrix pipe and the softmax's vector work on the same
 // SIMD, and, on long prefills, the card's power (MFMA alone on such operands
@@ -545,14 +609,14 @@ __device__ __forceinline__ void store_output(const PrefillParams& p, const ItemS
 // LDS buffers: K(j-1) and V(j) are read in step j; K(j-2) is stored over K(j)
 // and V(j-1) over V(j+1), both read in step j+1, before its barrier.
 template <int SEED, bool MX, int PV, int WAVES, int ABL = 0>
-__device__ __forceinline__ void prefill_item(const PrefillParams& p, int bid, PrefillSmemT<MX, PV>& sm) {
+__device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int h, int r0, PrefillSmemT<MX, PV>& sm) {
   constexpr int kUnits = 8 / WAVES;   // units of a tile per thread
   constexpr bool kSmooth = SEED != kSeedNone;
   // BF16 V: its 16 registers per thread are held only across the PV product
   // (across the whole step they spill)
   constexpr bool kLateV = PV == kPvBf16;
   ItemState st;
-  if (!item_setup<MX, WAVES>(p, bid, st)) return;
+  item_setup<MX, WAVES>(p, b, h, r0, st);
 
   SoftState ss = {-INFINITY, 0.0f, 0.0f};
   f32x16 o[4];
@@ -603,15 +667,17 @@ __device__ __forceinline__ void prefill_item(const PrefillParams& p, int bid, Pr
     pgn[u] = page(j_hi - 1, u);
   }
   load_k();
+#pragma unroll
+  for (int u = 0; u < kUnits; ++u) pgv[u] = pgk[u];
+  load_v();
   put_k(j_hi);
   next_pages(j_hi - 2);
-  load_k();
-  load_v();
-  put_k(j_hi - 1);
+  if (j_hi > 0) load_k();
   put_v(j_hi, st.kvl - j_hi * kTile);
+  if (j_hi > 0) put_k(j_hi - 1);
   __syncthreads();
   if (!st.wave_active) {   // a wave without rows only moves its share of the tiles
-    __syncthreads();
+    if (j_hi > 0) __syncthreads();
     for (int j = j_hi; j > 0; --j) {
       next_pages(j - 3);
       load_k();
@@ -627,7 +693,7 @@ __device__ __forceinline__ void prefill_item(const PrefillParams& p, int bid, Pr
   PTile pt;
 #pragma unroll
   for (int kb = 0; kb < 4; ++kb) qk_block<SEED, MX, PV>(s[kb], kb, sm, j_hi & 1, st);
-  __syncthreads();   // K of tile j_hi is read: the first step stores over it
+  if (j_hi > 0) __syncthreads();   // K of tile j_hi is read: the first step stores over it
   if (j_hi * kTile + kTile - 1 > st.wpos_min) mask_tile(s, j_hi * kTile, st);
   float alpha = max_tile<PV, ABL>(s, st, ss);
   float ps = exp_block<PV, ABL>(s[0], 0, st, ss, pt);
@@ -669,6 +735,18 @@ __device__ __forceinline__ void prefill_item(const PrefillParams& p, int bid, Pr
 #pragma unroll
   for (int db = 0; db < 4; ++db) asm volatile("" : "+v"(o[db]));
   store_output(p, st, ss.l, o);
+}
+
+// The item at position `bid` of the dispatch order (largest row tiles first).
+template <int SEED, bool MX, int PV, int ABL = 0>
+__device__ __forceinline__ void prefill_block(const PrefillParams& p, int bid, PrefillSmemT<MX, PV>& sm) {
+  int b, h, rank;
+  map_item(p, bid, b, h, rank);
+  int tile = p.n_qtiles - 1 - rank;
+  if (starts_differ(p) && !longest_item(p, rank * p.batch + b, b, tile)) return;
+  const int r0 = tile * kItemRows;
+  if (r0 >= p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b]) return;
+  prefill_item<SEED, MX, PV, kItemWaves, ABL>(p, b, h, r0, sm);
 }
 
 }  // namespace
