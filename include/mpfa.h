@@ -311,8 +311,8 @@ mpfa_status mpfa_decode_paged_static(const mpfa_decode_args* args, mpfa_stream_t
 /*
  * Runs the causal prefill described by `prefill` and the split-KV decode
  * described by `decode` in a single kernel launch, merge included (the last
- * partition of each (sequence, KV head) merges its query heads): decode
- * partitions first, then the prefill query tiles, in one grid.
+ * partition of each (sequence, KV head) merges its query heads): the prefill
+ * query tiles first, then the decode partitions, in one grid.
  * Results are bit-identical to mpfa_prefill followed by mpfa_decode_paged
  * with the same arguments.  Both parts must use the same MPFA_SMOOTH /
  * MPFA_MXFP4 setting (else MPFA_ERR_INVALID); the prefill flags may not

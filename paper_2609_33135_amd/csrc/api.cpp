@@ -441,10 +441,7 @@ mpfa_status mpfa_mixed_step(const mpfa_prefill_args* prefill, const mpfa_decode_
   const int64_t pre_rounds = (n_pre + 7) / 8;
   if (n_pre + 64 * n_rounds + 8 > INT32_MAX) return MPFA_ERR_INVALID;
   m.n_pre_blocks = (int)n_pre;
-  m.n_dec_rounds = (int)n_rounds;
-  // decode rounds first, back to back, then the prefill items (see mixed.hip)
-  m.stride = 1;
-  m.first = 0;
+  m.first = (int)(8 * pre_rounds);   // decode after the prefill items (see mixed.hip)
   m.n_blocks = (int)(8 * (pre_rounds + n_rounds));
 #ifdef MPFA_DEBUG_CHECKS
   st = check_prefill(prefill, reinterpret_cast<hipStream_t>(stream));

@@ -74,7 +74,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void decode_kernel(DecodePa
   if (!PACKED) {
     // grid (partition group, KV head, sequence); groups past the sequence's
     // partitions return inside decode_partition
-    decode_partition<SMOOTH, MX, false>(p, blockIdx.z, blockIdx.y, blockIdx.x * kWavesPerBlock + wave, nullptr);
+    decode_partition<SMOOTH, MX>(p, blockIdx.z, blockIdx.y, blockIdx.x * kWavesPerBlock + wave);
     return;
   }
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
@@ -102,7 +102,7 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void decode_kernel(DecodePa
     base += total;
   }
   if (b < 0) return;   // the grid is sized for batch * ceil(max_partitions / 4) pairs
-  decode_partition<SMOOTH, MX, false>(p, b, hk, grp * kWavesPerBlock + wave, nullptr);
+  decode_partition<SMOOTH, MX>(p, b, hk, grp * kWavesPerBlock + wave);
 }
 
 // Merge of the partition states, one workgroup per (query head, sequence).  A
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(WAVES * 64, 1) void decode_group_kernel(DecodeParam
   extern __shared__ __attribute__((aligned(16))) float states[];   // [WAVES][grp][kD + 2]
   const int hk = blockIdx.x, b = blockIdx.y, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int grp = p.h_q / p.h_kv, slice = grp * (kD + 2);
-  decode_partition<SMOOTH, MX, false, true>(p, b, hk, wave, nullptr, states + wave * slice);
+  decode_partition<SMOOTH, MX, true>(p, b, hk, wave, states + wave * slice);
   __syncthreads();
   const int np = (p.kv_len[b] + p.partition_tokens - 1) / p.partition_tokens;
   for (int j = wave; j < grp; j += WAVES) {

@@ -104,15 +104,12 @@ __device__ __forceinline__ void merge_head(const DecodeParams& p, int b, int h, 
 }
 
 // One decode work item (sequence b, KV head hk, partition part) executed by
-// one wave; it writes the partition state to the workspace.  With FUSED, the
-// wave then counts itself in counters[b * h_kv + hk] (device scope); the wave
-// that completes the last partition of (b, hk) merges the group's query heads,
-// writes the outputs and resets the counter to zero for the next call.  With
-// TO_LDS the state of query head hk * grp + j goes to lds + j * (kD + 2) instead
-// (this partition's slice, the caller's).
-template <bool SMOOTH, bool MX, bool FUSED, bool TO_LDS = false>
+// one wave; it writes the partition state to the workspace, or with TO_LDS the
+// state of query head hk * grp + j to lds + j * (kD + 2) (this partition's
+// slice, the caller's).
+template <bool SMOOTH, bool MX, bool TO_LDS = false>
 __device__ __forceinline__ void decode_partition(const DecodeParams& p, int b, int hk, int part,
-                                                 uint32_t* counters, float* lds = nullptr) {
+                                                 float* lds = nullptr) {
   // the item indices are wave-uniform: in scalar registers, the tile loop and
   // its branches are scalar too
   b = __builtin_amdgcn_readfirstlane(b);
@@ -353,18 +350,6 @@ __device__ __forceinline__ void decode_partition(const DecodeParams& p, int b, i
     for (int db = 0; db < 8; ++db)
 #pragma unroll
       for (int i = 0; i < 4; ++i) st[2 + 16 * db + 4 * g + i] = o[db][i];
-  }
-  if (FUSED) {
-    // release: this partition's state is visible device-wide before it is counted
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-    uint32_t prev = 0;
-    if (lane == 0) prev = atomicAdd(&counters[b * p.h_kv + hk], 1u);
-    prev = __shfl(prev, 0);
-    if (prev == (uint32_t)(np - 1)) {   // last partition of (b, hk): merge its query heads
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // every state counted before is visible
-      for (int j = 0; j < grp; ++j) merge_head<kMergeChunk>(p, b, hk * grp + j, np);
-      if (lane == 0) atomicExch(&counters[b * p.h_kv + hk], 0u);
-    }
   }
 }
 

@@ -12,10 +12,13 @@
 //
 // Placement: a prefill workgroup holds a whole compute unit (its LDS and all
 // of its registers), so prefill and decode cannot share a unit at the same
-// time; decode rounds spread through the prefill only take unit time from it
-// (measured slower than two launches).  The host therefore places the decode
-// rounds first: they stream the KV pages at full bandwidth on every unit, then
-// the prefill tiles follow in their largest-first order.
+// time; but the prefill's last round of items leaves units idle, and the decode
+// groups, dispatched after the prefill items, fill them.  4096 rows behind 16384
+// tokens and 64 decoding sequences, 40:8: 1362 us, 1624 with the decode first,
+// 1626 for the two calls; 2048 behind 8000 and 32 x 4000 keys 420 / 485 / 470;
+// 16384-token prompt and 64 x 6000 keys 2251 / 2258 / 2316; the decode first is the
+// better one only for a short prompt beside a long decode (1000 tokens, 16 x
+// 30000 keys: 263 / 253 / 204).
 #include <type_traits>
 
 #include "decode_body.h"
@@ -26,40 +29,53 @@ namespace mpfa {
 
 namespace {
 
-// Blocks are dealt to the 8 XCDs round-robin, so the grid is laid out in rounds
-// of 8 consecutive blocks.  Decode rounds (8 groups of 8 decode work items)
-// sit at round indices first, first + stride, ...; prefill items fill the
-// other rounds in their own order (largest query tiles first).  Whole rounds keep
-// every prefill item on the XCD its index selects (index = block - 8 * decode
-// rounds before it, the same residue mod 8), so the KV-head-per-XCD placement
-// of the prefill items holds as in the separate launch.
+// Blocks are dealt to the 8 XCDs round-robin: the prefill items come first, in
+// their own order (largest query tiles first), on the XCDs they have in the
+// separate launch; then, from the next multiple of 8, the decode groups of 8
+// work items.
 // FEW: the prefill items are those of prefill_few_kernel (the same bytes as the
 // separate calls either way).
 template <bool SMOOTH, bool MX, bool FEW>
 __global__ __launch_bounds__(512, 1) void mixed_kernel(MixedParams m) {
   __shared__ __attribute__((aligned(16))) std::conditional_t<FEW, FewSmem<SMOOTH, MX>, PrefillSmemT<MX, kPvFp8>> lds;
-  const int i = blockIdx.x, r = i >> 3;
-  // decode round k sits at round first + k * stride (k < n_dec_rounds)
-  const int rel = r - m.first;
-  const bool is_dec = rel >= 0 && rel % m.stride == 0 && rel / m.stride < m.n_dec_rounds;
-  const int dec_before = rel < 0 ? 0 : min(rel / m.stride + 1, m.n_dec_rounds);   // rounds <= r
-  if (!is_dec) {
-    const int bid = i - 8 * dec_before;
-    if (bid >= m.n_pre_blocks) return;
+  const int i = blockIdx.x;
+  if (i < m.first) {
+    if (i >= m.n_pre_blocks) return;
+    const int bid = i;
     if constexpr (FEW) prefill_few_block<SMOOTH, MX>(m.pre, bid, lds);
     else prefill_block<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8>(m.pre, bid, lds);
     return;
   }
-  // decode group (round, lane of the round): wave w takes item 8 * group + w =
-  // ((b * h_kv + hk) * max_partitions + part)
+  // decode group: wave w takes item 8 * group + w = ((b * h_kv + hk) *
+  // max_partitions + part)
   const int wave = threadIdx.x >> 6;
-  const int item = ((dec_before - 1) * 8 + (i & 7)) * 8 + wave;
+  const int item = (i - m.first) * 8 + wave;
   const DecodeParams& p = m.dec;
   const int part = item % p.max_partitions;
   const int hk = (item / p.max_partitions) % p.h_kv;
   const int b = item / (p.max_partitions * p.h_kv);
-  if (b >= p.batch) return;
-  decode_partition<SMOOTH, MX, true>(p, b, hk, part, m.counters);
+  const bool live = b < p.batch;
+  if (live) decode_partition<SMOOTH, MX>(p, b, hk, part);
+  // Release: the group's states become visible device-wide before any of its
+  // waves counts itself.  One write-back of the XCD's L2 per workgroup, between
+  // two barriers: one per wave (eight times as many) cost more than the decode
+  // itself (1000-token prompt and 16 x 30000 keys: 498 -> 253 us).
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's states are in the L2
+  __syncthreads();
+  if (wave == 0) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+  __syncthreads();
+  if (!live) return;
+  const int np = (p.kv_len[b] + p.partition_tokens - 1) / p.partition_tokens;
+  if (part >= np) return;
+  uint32_t prev = 0;
+  if ((threadIdx.x & 63) == 0) prev = atomicAdd(&m.counters[b * p.h_kv + hk], 1u);
+  prev = __shfl(prev, 0);
+  if (prev != (uint32_t)(np - 1)) return;
+  // the last partition of (b, hk): merge its query heads, reset the counter
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // every state counted before is visible
+  const int grp = p.h_q / p.h_kv;
+  for (int j = 0; j < grp; ++j) merge_head<kMergeChunk>(p, b, hk * grp + j, np);
+  if ((threadIdx.x & 63) == 0) atomicExch(&m.counters[b * p.h_kv + hk], 0u);
 }
 
 template <bool SMOOTH, bool MX>
