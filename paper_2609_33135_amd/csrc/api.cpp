@@ -21,6 +21,7 @@ namespace {
 
 constexpr int kPrefillRows = 256;   // query rows per prefill workgroup
 constexpr int kFewRows = 32;        // the same for calls with few query rows
+constexpr int kHalfBlocks = 416;    // most workgroups of 128 rows (see prefill_half_kernel)
 constexpr int kMaxKvHeads = mpfa::kMaxKvHeadsQuant;
 constexpr int kMaxDecodeGroup = 8;  // query heads per KV head packed in one decode wave
 constexpr float kLambda = 0.12751743074173085f;   // log2(e) / sqrt(128)
@@ -119,12 +120,18 @@ mpfa_status check_decode(const mpfa_decode_args* a, hipStream_t s) {
 
 }  // namespace
 
+// The method's placements (seed in the accumulator or none, FP8 PV): what the
+// kernels of other workgroup sizes are built for; the options run the 256-row one.
+static bool own_kernels(uint32_t flags) {
+  return !(flags & (MPFA_SEED_MFMA | MPFA_SEED_ELEMWISE | MPFA_PV_BF16 | MPFA_PV_NVFP4));
+}
+
 // Whether a call may gain from 32-row workgroups (prefill_few_block, which decides
 // per sequence): the method's own kernels, at most 8 such blocks per compute
 // unit, and a page table that leaves room for a context long enough to pay (the
 // lengths themselves are on the device).
 static bool prefill_few(const mpfa_prefill_args* a) {
-  if (a->flags & (MPFA_SEED_ELEMWISE | MPFA_PV_BF16 | MPFA_PV_NVFP4)) return false;
+  if (!own_kernels(a->flags)) return false;
   const int64_t blocks = ((int64_t)a->max_seqlen_q + kFewRows - 1) / kFewRows * a->h_q * a->batch;
   if (blocks > 8 * mpfa::kComputeUnits) return false;
   // the least blocks per compute unit: those of the longest sequence alone
@@ -135,7 +142,9 @@ static bool prefill_few(const mpfa_prefill_args* a) {
 }
 
 // Host-side validation of the prefill arguments and their launch parameters.
-static mpfa_status prefill_params(const mpfa_prefill_args* a, mpfa::PrefillParams& p) {
+// may_halve: 128-row workgroups may be chosen (not in the mixed step's grid of
+// 512-thread ones).
+static mpfa_status prefill_params(const mpfa_prefill_args* a, mpfa::PrefillParams& p, bool may_halve) {
   if (!a) return MPFA_ERR_INVALID;
   if (a->head_dim != MPFA_HEAD_DIM) return a->head_dim > 0 ? MPFA_ERR_UNSUPPORTED : MPFA_ERR_INVALID;
   if (a->batch < 1 || a->max_seqlen_q < 0 || a->max_pages < 1) return MPFA_ERR_INVALID;
@@ -166,7 +175,10 @@ static mpfa_status prefill_params(const mpfa_prefill_args* a, mpfa::PrefillParam
   p.order = a->batch > 1 && a->batch <= mpfa::kOrderMaxBatch && a->max_pages > 16 &&
             n_qtiles * a->h_q * (int64_t)a->batch > mpfa::kComputeUnits;
   p.few = prefill_few(a);
-  p.n_qtiles = p.few ? (a->max_seqlen_q + kFewRows - 1) / kFewRows : (int)n_qtiles;
+  const int64_t halves = ((int64_t)a->max_seqlen_q + kPrefillRows / 2 - 1) / (kPrefillRows / 2);
+  p.half = may_halve && !p.few && !p.order && halves > 1 && halves * a->h_q * a->batch <= kHalfBlocks &&
+           own_kernels(a->flags);
+  p.n_qtiles = p.few ? (a->max_seqlen_q + kFewRows - 1) / kFewRows : (int)(p.half ? halves : n_qtiles);
   p.smooth = smooth;
   p.seed_mfma = (a->flags & MPFA_SEED_MFMA) != 0;
   p.seed_elem = (a->flags & MPFA_SEED_ELEMWISE) != 0;
@@ -338,7 +350,7 @@ mpfa_status mpfa_quantize_qk(const mpfa_quant_args* a, mpfa_stream_t stream) {
 
 mpfa_status mpfa_prefill(const mpfa_prefill_args* a, mpfa_stream_t stream) {
   mpfa::PrefillParams p;
-  mpfa_status st = prefill_params(a, p);
+  mpfa_status st = prefill_params(a, p, true);
   if (st != MPFA_OK) return st;
 #ifdef MPFA_DEBUG_CHECKS
   st = check_prefill(a, reinterpret_cast<hipStream_t>(stream));
@@ -423,7 +435,7 @@ mpfa_status mpfa_mixed_step(const mpfa_prefill_args* prefill, const mpfa_decode_
   if ((prefill->flags & (MPFA_SMOOTH | MPFA_MXFP4)) != (decode->flags & (MPFA_SMOOTH | MPFA_MXFP4)))
     return MPFA_ERR_INVALID;
   mpfa::MixedParams m{};
-  mpfa_status st = prefill_params(prefill, m.pre);
+  mpfa_status st = prefill_params(prefill, m.pre, false);
   if (st != MPFA_OK) return st;
   size_t need = 0;
   if (mpfa_mixed_workspace_size(decode->batch, decode->h_q, decode->h_kv, decode->max_partitions, &need) !=

@@ -43,7 +43,7 @@ __global__ __launch_bounds__(512, 1) void mixed_kernel(MixedParams m) {
     if (i >= m.n_pre_blocks) return;
     const int bid = i;
     if constexpr (FEW) prefill_few_block<SMOOTH, MX>(m.pre, bid, lds);
-    else prefill_block<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8>(m.pre, bid, lds);
+    else prefill_block<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8, kItemWaves>(m.pre, bid, lds);
     return;
   }
   // decode group: wave w takes item 8 * group + w = ((b * h_kv + hk) *

@@ -738,15 +738,15 @@ __device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int 
 }
 
 // The item at position `bid` of the dispatch order (largest row tiles first).
-template <int SEED, bool MX, int PV, int ABL = 0>
+template <int SEED, bool MX, int PV, int WAVES, int ABL = 0>
 __device__ __forceinline__ void prefill_block(const PrefillParams& p, int bid, PrefillSmemT<MX, PV>& sm) {
   int b, h, rank;
   map_item(p, bid, b, h, rank);
   int tile = p.n_qtiles - 1 - rank;
-  if (starts_differ(p) && !longest_item(p, rank * p.batch + b, b, tile)) return;
-  const int r0 = tile * kItemRows;
+  if (WAVES == kItemWaves && starts_differ(p) && !longest_item(p, rank * p.batch + b, b, tile)) return;
+  const int r0 = tile * (WAVES * kWaveRows);
   if (r0 >= p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b]) return;
-  prefill_item<SEED, MX, PV, kItemWaves, ABL>(p, b, h, r0, sm);
+  prefill_item<SEED, MX, PV, WAVES, ABL>(p, b, h, r0, sm);
 }
 
 }  // namespace
