@@ -109,25 +109,54 @@ __global__ __launch_bounds__(kWavesPerBlock * 64, 2) void decode_kernel(DecodePa
 // separate launch: merging in the last-arriving decode wave needs the partition
 // states made visible across the XCDs' L2 caches (an L2 write-back per wave, or
 // write-through stores and an arrival counter), which measured slower than this
-// second launch.  The states are read once, a chunk's 32 rows in flight per
-// wave; what it costs is the round trips, so past one chunk eight waves share
-// the chunks, a round of eight at a time (one sequence of 131072 keys, 512
-// partitions, 40 heads: 75 -> 10 us; 17 partitions 5.6 -> 3.5 us).
-template <int WAVES, int N>
-__global__ __launch_bounds__(WAVES * 64) void merge_kernel(DecodeParams p) {
+// second launch.  Up to 32 partitions one wave merges them (17 partitions 5.6 ->
+// 3.5 us).
+template <int N>
+__global__ __launch_bounds__(64) void merge_kernel(DecodeParams p) {
   const int h = blockIdx.x, b = blockIdx.y;
+  merge_head<N>(p, b, h, (p.kv_len[b] + p.partition_tokens - 1) / p.partition_tokens);
+}
+
+// More than one chunk: WAVES waves share the chunks, a round of WAVES at a time.
+// The states are read once, a chunk's 32 rows in flight per wave; what it costs is
+// the round trips and what one compute unit can fetch (512 partitions: 266 KB per
+// head), so few heads are merged by two workgroups of 64 channels each (CH = 1
+// channel per lane instead of 2), of sixteen waves.  The sums and their order are
+// the same in each.  One sequence of 131072 keys, 40 heads: 75 us by one wave, 10
+// by eight, 7.5 by 2 x 16 (the whole call 48.0 -> 45.2; 500000 keys 181.7 ->
+// 175.8).  With more heads the two read the (m, l) twice for nothing (2 x 30000
+// keys 32:8 24.7 / 24.3, but 4 x 30000 41.3 / 41.3, 4 x 9000 40:8 22.3 / 24.4, 8 x
+// 30000 89.2 / 92.0).
+constexpr int kSplitMergeHeads = 64;
+
+template <int WAVES, int CH>
+__global__ __launch_bounds__(WAVES * 64) void merge_wide_kernel(DecodeParams p) {
+  constexpr int SLICES = 2 / CH;
+  const int h = blockIdx.x / SLICES, b = blockIdx.y;
   const int np = (p.kv_len[b] + p.partition_tokens - 1) / p.partition_tokens;
-  if (WAVES == 1) {
-    merge_head<N>(p, b, h, np);
-    return;
-  }
   __shared__ float wave_top[WAVES];
-  __shared__ float2 part_o[WAVES][64];
+  __shared__ float part_o[WAVES][CH][64];
   __shared__ float part_l[WAVES];
   const float* st = head_states(p, b, h);
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  float2 o[N];
-  if (wave * kMergeChunk < np) merge_load(st, wave * kMergeChunk, np, o);
+  const int ch = (blockIdx.x % SLICES) * 64 + CH * lane;   // this lane's first channel
+  float o[kMergeChunk][CH];
+  float2 ml = {};
+  auto load = [&](int q0) {   // all in flight; past np the last partition repeats and is not used
+    ml = merge_ml(st, q0, np);
+#pragma unroll
+    for (int j = 0; j < kMergeChunk; ++j) {
+      const float* row = st + (int64_t)min(q0 + j, np - 1) * (kD + 2) + 2 + ch;
+      if constexpr (CH == 2) {
+        const float2 v = *reinterpret_cast<const float2*>(row);
+        o[j][0] = v.x;
+        o[j][1] = v.y;
+      } else {
+        o[j][0] = *row;
+      }
+    }
+  };
+  if (wave * kMergeChunk < np) load(wave * kMergeChunk);
   float M = -INFINITY;
   for (int q = threadIdx.x; q < np; q += WAVES * 64) M = fmaxf(M, st[(int64_t)q * (kD + 2)]);
   M = wave_max64(M);
@@ -135,26 +164,39 @@ __global__ __launch_bounds__(WAVES * 64) void merge_kernel(DecodeParams p) {
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < WAVES; ++w) M = fmaxf(M, wave_top[w]);
-  float L = 0.0f, O0 = 0.0f, O1 = 0.0f;   // wave 0
+  float L = 0.0f, O[CH] = {};   // wave 0
   for (int r0 = 0; r0 < np; r0 += WAVES * kMergeChunk) {
     const int q0 = r0 + wave * kMergeChunk;
     if (q0 < np) {
-      if (r0 > 0) merge_load(st, q0, np, o);
-      const MergeSum c = merge_chunk(o, merge_ml(st, q0, np), q0, np, M);
-      part_o[wave][lane] = make_float2(c.o0, c.o1);
-      if (lane == 0) part_l[wave] = c.l;
+      if (r0 > 0) load(q0);
+      const float f = __builtin_amdgcn_exp2f(ml.x - M);
+      float l = 0.0f, s[CH] = {};
+#pragma unroll
+      for (int j = 0; j < kMergeChunk; ++j) {
+        if (q0 + j < np) {
+          const float fj = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(f), j));
+          l = __builtin_fmaf(fj, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(ml.y), j)), l);
+#pragma unroll
+          for (int i = 0; i < CH; ++i) s[i] = __builtin_fmaf(fj, o[j][i], s[i]);
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < CH; ++i) part_o[wave][i][lane] = s[i];
+      if (lane == 0) part_l[wave] = l;
     }
     __syncthreads();
     if (wave == 0) {
       for (int w = 0; w < WAVES && r0 + w * kMergeChunk < np; ++w) {
         L += part_l[w];
-        O0 += part_o[w][lane].x;
-        O1 += part_o[w][lane].y;
+#pragma unroll
+        for (int i = 0; i < CH; ++i) O[i] += part_o[w][i][lane];
       }
     }
     __syncthreads();
   }
-  if (wave == 0) merge_store(p, b, h, L, O0, O1, np > 0);
+  if (wave != 0) return;
+  if constexpr (CH == 2) merge_store(p, b, h, L, O[0], O[1], np > 0);
+  else p.out[((int64_t)b * p.h_q + h) * kD + ch] = (uint16_t)bf16_rne(np > 0 ? __fdiv_rn(O[0], L) : 0.0f);
 }
 
 // Short contexts: one workgroup per (KV head, sequence) whose waves are its
@@ -243,10 +285,11 @@ hipError_t launch_decode(const DecodeParams& p, hipStream_t stream) {
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  if (p.max_partitions <= 8) merge_kernel<1, 8><<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
-  else if (p.max_partitions <= 16) merge_kernel<1, 16><<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
-  else if (p.max_partitions <= kMergeChunk) merge_kernel<1, kMergeChunk><<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
-  else merge_kernel<8, kMergeChunk><<<dim3(p.h_q, p.batch), dim3(512), 0, stream>>>(p);
+  if (p.max_partitions <= 8) merge_kernel<8><<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
+  else if (p.max_partitions <= 16) merge_kernel<16><<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
+  else if (p.max_partitions <= kMergeChunk) merge_kernel<kMergeChunk><<<dim3(p.h_q, p.batch), dim3(64), 0, stream>>>(p);
+  else if (p.h_q * (int64_t)p.batch <= kSplitMergeHeads) merge_wide_kernel<16, 1><<<dim3(2 * p.h_q, p.batch), dim3(1024), 0, stream>>>(p);
+  else merge_wide_kernel<8, 2><<<dim3(p.h_q, p.batch), dim3(512), 0, stream>>>(p);
   return hipGetLastError();
 }
 

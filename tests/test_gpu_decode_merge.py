@@ -61,3 +61,11 @@ def test_mixed_merge_same_bytes(orc, mp, nparts):
                             partition_tokens=128, max_partitions=nparts), ws, mp.SMOOTH)
     torch.cuda.synchronize()
     assert np.array_equal(H.bits(dec), ref)
+
+
+@pytest.mark.parametrize("h_q,h_kv,batch,nparts", [(32, 8, 2, 33), (33, 11, 2, 33), (40, 8, 2, 40), (2, 1, 1, 515)])
+def test_split_merge_limit(orc, mp, h_q, h_kv, batch, nparts):
+    """Both sides of the 64 heads that two workgroups per head merge, and a second round of sixteen waves."""
+    lens = [nparts * 128 - 5, 128 * 32 + 1][:batch]
+    run = H.Run(orc, mp, 74, lens, h_q, h_kv)
+    _check(run.decode_last_gpu(128), run.decode_last_oracle(128))
