@@ -238,8 +238,10 @@ __global__ __launch_bounds__(64) void stats_partial_wave_kernel(QuantParams p) {
 // slice, sequence), so that the partials of one head are read by four compute
 // units.  The slice's partials arrive in LDS 256 blocks at a time (coalesced
 // 128-byte rows, the next chunk in flight while the current one is added);
-// threads 0..31 own one channel each and add its partials strictly in block
-// order, then FP32 divide and BF16 rounding.  The tensor scale needs the amax
+// 32 lanes of wave 0 own one channel each and add its partials strictly in block
+// order, then FP32 divide and BF16 rounding; waves 1 and 2 take the maxima and
+// minima beside them (one wave for the three walked the chunk three times as
+// long: 131072 tokens 40:8 34.5 -> 27 us, 75 MB of partials).  The tensor scale needs the amax
 // of the whole head: each slice stores its own and counts itself in the
 // head's arrival counter; the fourth arrival takes the maximum and writes the
 // scale.  Counters and slice amaxes live in the spare bytes of the first
@@ -289,6 +291,7 @@ __global__ __launch_bounds__(kFinThreads) void stats_final_kernel(QuantParams p)
   const int c0 = slice * kFinSlice, c = c0 + t;
   float tot = 0.0f, mx = -INFINITY, mn = INFINITY;
   {
+    const int arr = t >> 6, lane = t & 63;   // waves 0, 1, 2: sum, max, min
     float4 r[kFinLoads];
     fin_load(p, t0, nblk, ss.hs, hh, c0, 0, r);
     for (int blk0 = 0; blk0 < nblk; blk0 += kFinChunk) {
@@ -296,18 +299,30 @@ __global__ __launch_bounds__(kFinThreads) void stats_final_kernel(QuantParams p)
       for (int i = 0; i < kFinLoads; ++i) chunk[i * kFinThreads + t] = r[i];
       __syncthreads();
       if (blk0 + kFinChunk < nblk) fin_load(p, t0, nblk, ss.hs, hh, c0, blk0 + kFinChunk, r);
-      if (t < kFinSlice) {
-        const float* cs = reinterpret_cast<const float*>(chunk);
+      if (lane < kFinSlice) {
+        const float* cs = reinterpret_cast<const float*>(chunk) + arr * kFinChunk * kFinSlice + lane;
         const int nb = min(kFinChunk, nblk - blk0);
-        // unrolled so that the LDS reads run ahead of the dependent additions
+        // unrolled so that the LDS reads run ahead of the dependent operations
+        if (arr == 0) {
 #pragma unroll 16
-        for (int j = 0; j < nb; ++j) {
-          tot += cs[j * kFinSlice + t];
-          mx = fmaxf(mx, cs[(kFinChunk + j) * kFinSlice + t]);
-          mn = fminf(mn, cs[(2 * kFinChunk + j) * kFinSlice + t]);
+          for (int j = 0; j < nb; ++j) tot += cs[j * kFinSlice];
+        } else if (arr == 1) {
+#pragma unroll 16
+          for (int j = 0; j < nb; ++j) mx = fmaxf(mx, cs[j * kFinSlice]);
+        } else if (arr == 2) {
+#pragma unroll 16
+          for (int j = 0; j < nb; ++j) mn = fminf(mn, cs[j * kFinSlice]);
         }
       }
       __syncthreads();
+    }
+    float* ends = reinterpret_cast<float*>(chunk);   // [max, min][channel]
+    if (lane < kFinSlice && arr == 1) ends[lane] = mx;
+    if (lane < kFinSlice && arr == 2) ends[kFinSlice + lane] = mn;
+    __syncthreads();
+    if (t < kFinSlice) {
+      mx = ends[t];
+      mn = ends[kFinSlice + t];
     }
   }
   if (t < 64) {   // one wave: the slice's 32 channels
