@@ -67,6 +67,11 @@ __device__ __forceinline__ void write_tscale(const QuantParams& p, int b, int hh
   else p.k_tscale[b * p.h_kv + (hh - p.h_q)] = ts;
 }
 
+// Rows read once by the workgroup, past the caches' ordinary replacement: 131072
+// tokens 40:8, 864 -> 812 us of the whole call (1.6 GB read by this kernel, 326 us
+// before); nothing lost where the inputs fit in the last-level cache (9000 tokens).
+__device__ __forceinline__ u32x4 load_stream(const u32x4* src) { return __builtin_nontemporal_load(src); }
+
 __global__ __launch_bounds__(256) void stats_partial_kernel(QuantParams p) {
   const int b = blockIdx.y, blk = blockIdx.x;
   const int64_t t0 = p.cu_seqlens[b];
@@ -79,7 +84,7 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(QuantParams p) {
   if (nblk >= 2 && blk == 0)   // arrival counters of stats_final_kernel
     for (int i = threadIdx.x; i < ss.hs; i += blockDim.x) reinterpret_cast<uint32_t*>(fin_scratch(p, t0, ss.hs))[i] = 0u;
   for (int u0 = 0; u0 < nunits; u0 += 256 * kStatUnits) {
-    const uint4* src[kStatUnits];
+    const u32x4* src[kStatUnits];
     int64_t stride[kStatUnits];   // in 16-byte words per token
     bool act[kStatUnits];
     float sm[kStatUnits][8], mx[kStatUnits][8], mn[kStatUnits][8];
@@ -92,7 +97,7 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(QuantParams p) {
       const int H = isq ? p.h_q : p.h_kv;
       const int h = isq ? hh : hh - p.h_q;
       const uint16_t* base = isq ? p.q : p.k;
-      src[k] = reinterpret_cast<const uint4*>(base + ((t0 + tb) * H + h) * kD + oct * 8);
+      src[k] = reinterpret_cast<const u32x4*>(base + ((t0 + tb) * H + h) * kD + oct * 8);
       stride[k] = (int64_t)H * (kD / 8);
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -102,12 +107,12 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(QuantParams p) {
       }
     }
     for (int t = tb; t < te; t += 4) {
-      uint4 w[4][kStatUnits];
+      u32x4 w[4][kStatUnits];
 #pragma unroll
       for (int j = 0; j < 4; ++j)
 #pragma unroll
         for (int k = 0; k < kStatUnits; ++k)
-          w[j][k] = (act[k] && t + j < te) ? src[k][(int64_t)(t - tb + j) * stride[k]] : make_uint4(0, 0, 0, 0);
+          w[j][k] = (act[k] && t + j < te) ? load_stream(src[k] + (int64_t)(t - tb + j) * stride[k]) : u32x4{0, 0, 0, 0};
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         if (t + j < te) {
@@ -681,10 +686,13 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams p) {
   __shared__ float rcp_sd[128];
   // [h_q + h_kv][kMeanStride] BF16 mean rows, then [h_q + h_kv] tensor scales
   extern __shared__ __attribute__((aligned(16))) uint8_t sm_mean[];
-  const int b = blockIdx.y;
+  // last tokens first: the statistics pass ended with them, so they are the ones
+  // still in the last-level cache (20000 + 9000 + 30000 + 12345 tokens 32:8 636 ->
+  // 509 us with the streaming loads of that pass, 598 with those alone)
+  const int b = gridDim.y - 1 - blockIdx.y;
   const int64_t t0 = p.cu_seqlens[b];
   const int n = p.cu_seqlens[b + 1] - (int)t0;
-  const int i0 = blockIdx.x * kChunk;
+  const int i0 = (int)(gridDim.x - 1 - blockIdx.x) * kChunk;
   if (i0 >= n) return;
   const int cnt = min(kChunk, n - i0);
   const int64_t tok0 = t0 + i0;
