@@ -120,18 +120,17 @@ mpfa_status check_decode(const mpfa_decode_args* a, hipStream_t s) {
 
 }  // namespace
 
-// The method's placements (seed in the accumulator or none, FP8 PV): what the
-// kernels of other workgroup sizes are built for; the options run the 256-row one.
-static bool own_kernels(uint32_t flags) {
-  return !(flags & (MPFA_SEED_MFMA | MPFA_SEED_ELEMWISE | MPFA_PV_BF16 | MPFA_PV_NVFP4));
-}
+// Flags that keep the 256-row kernel at every size.  MPFA_SEED_MFMA is not one of
+// them for the 32-row workgroups: their seed is formed that way for either flag, so
+// the two placements give the same bytes there too.
+constexpr uint32_t kWholeOnly = MPFA_SEED_ELEMWISE | MPFA_PV_BF16 | MPFA_PV_NVFP4;
 
 // Whether a call may gain from 32-row workgroups (prefill_few_block, which decides
 // per sequence): the method's own kernels, at most 8 such blocks per compute
 // unit, and a page table that leaves room for a context long enough to pay (the
 // lengths themselves are on the device).
 static bool prefill_few(const mpfa_prefill_args* a) {
-  if (!own_kernels(a->flags)) return false;
+  if (a->flags & kWholeOnly) return false;
   const int64_t blocks = ((int64_t)a->max_seqlen_q + kFewRows - 1) / kFewRows * a->h_q * a->batch;
   if (blocks > 8 * mpfa::kComputeUnits) return false;
   // the least blocks per compute unit: those of the longest sequence alone
@@ -177,7 +176,7 @@ static mpfa_status prefill_params(const mpfa_prefill_args* a, mpfa::PrefillParam
   p.few = prefill_few(a);
   const int64_t halves = ((int64_t)a->max_seqlen_q + kPrefillRows / 2 - 1) / (kPrefillRows / 2);
   p.half = may_halve && !p.few && !p.order && halves > 1 && halves * a->h_q * a->batch <= kHalfBlocks &&
-           own_kernels(a->flags);
+           !(a->flags & (kWholeOnly | MPFA_SEED_MFMA));
   p.n_qtiles = p.few ? (a->max_seqlen_q + kFewRows - 1) / kFewRows : (int)(p.half ? halves : n_qtiles);
   p.smooth = smooth;
   p.seed_mfma = (a->flags & MPFA_SEED_MFMA) != 0;
