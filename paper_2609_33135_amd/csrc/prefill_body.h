@@ -88,6 +88,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t page_rsrc(const void* base, in
 __device__ __forceinline__ u32x4 page_load16(const void* base, int bytes, uint32_t off, int scalar_off = 0) {
   return __builtin_amdgcn_raw_buffer_load_b128(page_rsrc(base, bytes), off, scalar_off, 0);
 }
+__device__ __forceinline__ uint2 page_load8(const void* base, int bytes, uint32_t off, int scalar_off = 0) {
+  const auto w = __builtin_amdgcn_raw_buffer_load_b64(page_rsrc(base, bytes), off, scalar_off, 0);
+  return make_uint2(w[0], w[1]);
+}
 __device__ __forceinline__ uint32_t page_load4(const void* base, int bytes, uint32_t off, int scalar_off = 0) {
   return __builtin_amdgcn_raw_buffer_load_b32(page_rsrc(base, bytes), off, scalar_off, 0);
 }
@@ -194,7 +198,7 @@ __device__ __forceinline__ void store_v(PrefillSmemT<MX, PV>& sm, int buf, const
 struct ItemState {
   int b, h, hk, q0, nq, qs, kvl, j_hi;
   int lane, wave, hf, lc;   // lane half (l / 32) and query column (l % 32)
-  int wrow0, wpos_min, wpos_max;
+  int wrow0, wpos_min;
   bool wave_active;
   float lam2, seed_scale;
   int pos;             // absolute position of the lane's query
@@ -283,14 +287,15 @@ __device__ __forceinline__ bool starts_differ(const PrefillParams& p) {
   return __ballot(abs(x - x0) > kItemRows) != 0;
 }
 
-// Work item of query head h, rows r0 .. of sequence b (r0 below its row count);
-// loads the wave's query operands.  SPLIT: the item is 32 rows shared by all
-// waves (prefill_split_item), else each wave has 32 rows of its own.
-template <bool MX, int WAVES, bool SPLIT = false>
-__device__ __forceinline__ void item_setup(const PrefillParams& p, int b, int h, int r0, ItemState& st) {
-  constexpr int kRows = SPLIT ? kWaveRows : WAVES * kWaveRows;
+// State of one wave of the work item (query head h, rows r0 .. r0 + rows - 1 of
+// sequence b, r0 below its row count); wrow0: the wave's first row.  Loads the
+// wave's query operands.
+template <bool MX>
+__device__ __forceinline__ void item_setup(const PrefillParams& p, int b, int h, int r0, int rows, int wrow0,
+                                           ItemState& st) {
   const int q0 = p.cu_seqlens_q[b];
   const int nq = p.cu_seqlens_q[b + 1] - q0;
+  const int end = min(r0 + rows, nq);
 
   st.b = b;
   st.h = h;
@@ -303,18 +308,16 @@ __device__ __forceinline__ void item_setup(const PrefillParams& p, int b, int h,
   st.wave = threadIdx.x >> 6;
   st.hf = st.lane >> 5;
   st.lc = st.lane & 31;
-  const int last_row = min(r0 + kRows, nq) - 1;
-  st.j_hi = (st.qs + last_row) >> 7;
+  st.j_hi = (st.qs + end - 1) >> 7;
 
   const float tq = p.q_tscale[b * p.h_q + h], tk = p.k_tscale[b * p.h_kv + st.hk];
   const int eqk = ilog2f(tq) + ilog2f(tk);
   st.lam2 = __builtin_ldexpf(p.lam, eqk);        // lambda * tQ * tK
   st.seed_scale = __builtin_ldexpf(1.0f, -eqk);  // Delta_S in accumulator units
 
-  st.wrow0 = r0 + (SPLIT ? 0 : st.wave * kWaveRows);
-  st.wave_active = st.wrow0 < nq;
+  st.wrow0 = wrow0;
+  st.wave_active = wrow0 < end;
   st.wpos_min = st.qs + st.wrow0;
-  st.wpos_max = st.qs + min(st.wrow0 + kWaveRows, nq) - 1;
 
   // ---- Q operands (B of S^T = K Q^T).  NVFP4: exact FP16, tensor scale
   // factored out.  MXFP4: the raw codes and E8M0 scales (the lane's 32-element
@@ -332,16 +335,14 @@ __device__ __forceinline__ void item_setup(const PrefillParams& p, int b, int h,
       st.qscale[i] = valid ? qsc[2 * i + st.hf] : 127;
     }
   } else {
-    // the lane's channels: 16ks + 8hf .. +7 (group ks), or 64hf + 8ks .. +7 (group
-    // 4hf + ks/2; contiguous code bytes); scale times code is exact in FP16
+    // the lane's channels: 16ks + 8hf .. +7 (group ks); scale times code is exact in FP16
     const uint2 sw = valid ? *reinterpret_cast<const uint2*>(qsc) : make_uint2(0u, 0u);
-    const uint32_t lo = SPLIT && st.hf ? sw.y : sw.x, hi = sw.y;
-    const f16x2 a = e4m3_pair_f16(lo), b2 = e4m3_pair_f16(lo >> 16), c = e4m3_pair_f16(hi), d = e4m3_pair_f16(hi >> 16);
+    const f16x2 a = e4m3_pair_f16(sw.x), b2 = e4m3_pair_f16(sw.x >> 16), c = e4m3_pair_f16(sw.y), d = e4m3_pair_f16(sw.y >> 16);
     const _Float16 g[8] = {a[0], a[1], b2[0], b2[1], c[0], c[1], d[0], d[1]};
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks) {
-      const uint32_t cw = valid ? *reinterpret_cast<const uint32_t*>(qc + (SPLIT ? 32 * st.hf + 4 * ks : 8 * ks + 4 * st.hf)) : 0u;
-      st.qop[ks] = dequant8h(cw, g[SPLIT ? ks >> 1 : ks]);
+      const uint32_t cw = valid ? *reinterpret_cast<const uint32_t*>(qc + 8 * ks + 4 * st.hf) : 0u;
+      st.qop[ks] = dequant8h(cw, g[ks]);
     }
   }
   st.bseed = (bf16x8){};
@@ -567,23 +568,26 @@ __device__ __forceinline__ void pv_tile(const PrefillSmemT<MX, PV>& sm, int buf,
 }
 
 // out = O / (448 l) as BF16 (for the other PV precisions the factor is the
-// one their P carries).
+// one their P carries): channels 32 db .. +31 of one row, inv = 1 / l.
+__device__ __forceinline__ void store_channels(const PrefillParams& p, const ItemState& st, int row, int db, float inv,
+                                               const f32x16& o) {
+  uint16_t* dst = p.out + ((int64_t)(st.q0 + row) * p.h_q + st.h) * kD + 32 * db + 4 * st.hf;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const uint32_t lo = (uint32_t)bf16_rne(o[4 * i] * inv) | ((uint32_t)bf16_rne(o[4 * i + 1] * inv) << 16);
+    const uint32_t hi = (uint32_t)bf16_rne(o[4 * i + 2] * inv) | ((uint32_t)bf16_rne(o[4 * i + 3] * inv) << 16);
+    *reinterpret_cast<uint2*>(dst + 8 * i) = make_uint2(lo, hi);
+  }
+}
+
 __device__ __forceinline__ void store_output(const PrefillParams& p, const ItemState& st, float l,
                                              const f32x16 (&o)[4]) {
   const float lt = l + __shfl_xor(l, 32);
   const int row = st.wrow0 + st.lc;
   if (row < st.nq) {
-    uint16_t* dst = p.out + ((int64_t)(st.q0 + row) * p.h_q + st.h) * kD;
     const float inv = __frcp_rn(lt);
 #pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const uint32_t lo = (uint32_t)bf16_rne(o[db][4 * i] * inv) | ((uint32_t)bf16_rne(o[db][4 * i + 1] * inv) << 16);
-        const uint32_t hi =
-            (uint32_t)bf16_rne(o[db][4 * i + 2] * inv) | ((uint32_t)bf16_rne(o[db][4 * i + 3] * inv) << 16);
-        *reinterpret_cast<uint2*>(dst + 32 * db + 8 * i + 4 * st.hf) = make_uint2(lo, hi);
-      }
+    for (int db = 0; db < 4; ++db) store_channels(p, st, row, db, inv, o[db]);
   }
 }
 
@@ -609,14 +613,15 @@ __device__ __forceinline__ void store_output(const PrefillParams& p, const ItemS
 // LDS buffers: K(j-1) and V(j) are read in step j; K(j-2) is stored over K(j)
 // and V(j-1) over V(j+1), both read in step j+1, before its barrier.
 template <int SEED, bool MX, int PV, int WAVES, int ABL = 0>
-__device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int h, int r0, PrefillSmemT<MX, PV>& sm) {
+__device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int h, int r0, PrefillSmemT<MX, PV>& sm,
+                                             int rows = WAVES * kWaveRows) {
   constexpr int kUnits = 8 / WAVES;   // units of a tile per thread
   constexpr bool kSmooth = SEED != kSeedNone;
   // BF16 V: its 16 registers per thread are held only across the PV product
   // (across the whole step they spill)
   constexpr bool kLateV = PV == kPvBf16;
   ItemState st;
-  item_setup<MX, WAVES>(p, b, h, r0, st);
+  item_setup<MX>(p, b, h, r0, rows, r0 + (int)(threadIdx.x >> 6) * kWaveRows, st);
 
   SoftState ss = {-INFINITY, 0.0f, 0.0f};
   f32x16 o[4];
@@ -709,7 +714,7 @@ __device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int 
       ps += exp_block<PV, ABL>(s[kb + 1], kb + 1, st, ss, pt);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (ABL < 2) ss.l = alpha * ss.l + ps;
+    if (ABL < 2) ss.l = __builtin_fmaf(alpha, ss.l, ps);
     qk_block<SEED, MX, PV>(s[3], 3, sm, kbuf, st);
     put_k(j - 2);
     if (!kLateV) put_v(j - 1, kTile);
@@ -726,7 +731,7 @@ __device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int 
 #pragma unroll
   for (int kb = 1; kb < 4; ++kb) ps += exp_block<PV, ABL>(s[kb], kb, st, ss, pt);
   if (ABL < 2) {
-    ss.l = alpha * ss.l + ps;
+    ss.l = __builtin_fmaf(alpha, ss.l, ps);
     rescale(o, alpha);
   }
   pv_tile<MX, PV>(sm, 0, pt, o, st);

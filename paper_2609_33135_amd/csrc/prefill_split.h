@@ -4,19 +4,21 @@
 // prefill_item walks a row block's tiles one after the other, so a call whose row
 // blocks do not fill the chip (a short prompt, a chunk behind a long prefix, few
 // heads on a tensor-parallel shard) takes (tiles) x (latency of a tile step).
-// Here wave w takes the tiles j with j % 8 == 7 - w, one per round.  The method
-// quantizes P at the running maximum, so a round first takes every tile's row
-// maximum, exchanges them through LDS, and each wave then uses the running
-// maximum its tile has in the sequential order (last tile to first): the same P
-// codes.  Every wave accumulates its own l and O relative to the maximum of its
-// latest tile; they are added at the end, scaled to the final maximum.  Only the
-// order of FP32 sums differs from prefill_item.
-//
-// A tile is used by one wave, so K and V go straight to registers as in the
-// decode (no LDS staging, and K is dequantized per wave instead of once per
-// workgroup: about 250 more vector instructions per tile and 32 rows).  That is
-// why prefill_item stays for calls that fill the chip (prefill_few_block has the
-// rule).
+// Here the scores and the softmax of eight tiles run side by side and only the PV
+// product, the short part of a step, walks the tiles in order:
+//   * wave w takes the tiles j with j % 8 == 7 - w, one per round: K and its own
+//     scores go straight to registers as in the decode (no LDS staging, K is
+//     dequantized per wave instead of once per workgroup: about 250 more vector
+//     instructions per tile and 32 rows);
+//   * the method quantizes P at the running maximum, so the waves exchange their
+//     tiles' row maxima through LDS; each then has the running maxima before and
+//     after its tile in the sequential order (last tile to first), and with them
+//     the tile's P codes, rescale factor and row sum, which it leaves in LDS;
+//   * a round later wave w < 4 accumulates O of channels 32w .. 32w + 31 over the
+//     eight tiles in that order, the other waves being in their softmax meanwhile
+//     (one such wave per SIMD).
+// Every FP32 operation has the operands and the order it has in prefill_item, so
+// the bytes are the same whichever of the two a call takes.
 #pragma once
 #include "prefill_body.h"
 
@@ -25,20 +27,21 @@ namespace mpfa {
 namespace {
 
 constexpr int kSplitWaves = 8;
-constexpr int kSplitStride = kD + 4;   // floats per O row in LDS (padded: rows on distinct banks)
+constexpr int kPvWaves = 4;       // 32 channels each
 
 struct SplitSmem {
-  float top[2][kSplitWaves][kWaveRows];          // row maxima of a round's tiles
-  float m[kSplitWaves][kWaveRows], l[kSplitWaves][kWaveRows];
-  float o[kSplitWaves][kWaveRows * kSplitStride];
+  float top[2][kSplitWaves][kWaveRows];        // row maxima of a round's tiles
+  float alpha[2][kSplitWaves][kWaveRows];      // their rescale factors
+  float ps[2][kSplitWaves][64];                // the lanes' row sums
+  u32x4 p[2][kSplitWaves][4][64];              // P codes as PV operands: [16-byte part][lane]
 };
 
 // K side of one tile in registers: lane (row r = lane % 32, half hf) holds, for
 // the key of MFMA row r of each 32-key block, channels 64hf .. +63 (NVFP4), or
-// 32hf .. +31 and 64 + 32hf .. +31 (MXFP4), their scales and the key's Delta_S.
+// 32hf .. +31 and 64 + 32hf .. +31 (MXFP4), the row's scales and the key's Delta_S.
 struct SplitK {
   u32x4 c[4][2];
-  uint32_t sc[4];
+  uint2 sc[4];
   uint32_t ds[4];
 };
 
@@ -51,15 +54,16 @@ __device__ __forceinline__ void split_load_k(SplitK& r, const PrefillParams& p, 
     const int pg = kb < 2 ? pg0 : pg1;
     const int64_t row = (int64_t)pg * p.h_kv + st.hk;
     const uint8_t* cb = p.k_codes + row * (kPage * 64);
+    const uint8_t* sb = p.k_scales + row * (kPage * 8);
     const int so = 16 * (kb & 1);   // keys, as a scalar offset
     if (MX) {
       r.c[kb][0] = page_load16(cb, kPage * 64, key0 * 64 + 16 * st.hf, so * 64);
       r.c[kb][1] = page_load16(cb, kPage * 64, key0 * 64 + 16 * st.hf, so * 64 + 32);
-      r.sc[kb] = page_load4(p.k_scales + row * (kPage * 8), kPage * 8, key0 * 8, so * 8);
+      r.sc[kb].x = page_load4(sb, kPage * 8, key0 * 8, so * 8);
     } else {
       r.c[kb][0] = page_load16(cb, kPage * 64, key0 * 64 + 32 * st.hf, so * 64);
       r.c[kb][1] = page_load16(cb, kPage * 64, key0 * 64 + 32 * st.hf, so * 64 + 16);
-      r.sc[kb] = page_load4(p.k_scales + row * (kPage * 8), kPage * 8, key0 * 8 + 4 * st.hf, so * 8);
+      r.sc[kb] = page_load8(sb, kPage * 8, key0 * 8, so * 8);
     }
     if (SMOOTH)
       r.ds[kb] = page_load2(p.ds + ((int64_t)pg * p.h_q + st.h) * kPage, kPage * 2, key0 * 2, so * 2);
@@ -80,77 +84,121 @@ __device__ __forceinline__ void split_qk(f32x16 (&s)[4], const SplitK& r, const 
       acc = mfma32_bf16(__builtin_bit_cast(bf16x8, a), st.bseed, acc);
     }
     if (MX) {
-      const int sc = (int)(r.sc[kb] >> (8 * st.hf));   // bytes 0, 2: blocks hf, 2 + hf
+      const int sc = (int)(r.sc[kb].x >> (8 * st.hf));   // bytes 0, 2: blocks hf, 2 + hf
       acc = mfma32_fp4<0>(r.c[kb][0], st.qraw[0], acc, sc, st.qscale[0]);
       acc = mfma32_fp4<2>(r.c[kb][1], st.qraw[1], acc, sc, st.qscale[1]);
     } else {
-      const f16x2 s01 = e4m3_pair_f16(r.sc[kb]), s23 = e4m3_pair_f16(r.sc[kb] >> 16);
+      // MFMA ks takes channels 16ks + 8hf .. +7, code dword 2ks + hf of the row.
+      // A lane half holds dwords 8hf .. +7: the swap of the upper half of dword 2t
+      // with the lower half of dword 2t + 1 gives the operands of ks = t and 4 + t.
+      uint32_t w[8];
 #pragma unroll
-      for (int ks = 0; ks < 8; ++ks)
-        acc = mfma32_f16(dequant8h(r.c[kb][ks >> 2][ks & 3], ks < 4 ? s01[ks >> 1] : s23[(ks >> 1) - 2]), st.qop[ks], acc);
+      for (int t = 0; t < 4; ++t) {
+        const auto x = __builtin_amdgcn_permlane32_swap(r.c[kb][t >> 1][2 * (t & 1)], r.c[kb][t >> 1][2 * (t & 1) + 1],
+                                                        false, false);
+        w[t] = x[0];
+        w[4 + t] = x[1];
+      }
+      const f16x2 a = e4m3_pair_f16(r.sc[kb].x), b = e4m3_pair_f16(r.sc[kb].x >> 16);
+      const f16x2 c = e4m3_pair_f16(r.sc[kb].y), d = e4m3_pair_f16(r.sc[kb].y >> 16);
+      const _Float16 g[8] = {a[0], a[1], b[0], b[1], c[0], c[1], d[0], d[1]};
+#pragma unroll
+      for (int ks = 0; ks < 8; ++ks) acc = mfma32_f16(dequant8h(w[ks], g[ks]), st.qop[ks], acc);
     }
     s[kb] = acc;
   }
 }
 
-// V of 64 keys (page pg) of the tile: A operands of the four channel blocks.
-__device__ __forceinline__ void split_load_v(u32x4 (&v)[4][2], const PrefillParams& p, const ItemState& st, int pg) {
-  const uint8_t* vb = p.v_codes + ((int64_t)pg * p.h_kv + st.hk) * (kD * kPage);
+// V of channel block db of one tile (pages pg0, pg1): the A operands of its two
+// 64-key MFMAs.
+__device__ __forceinline__ void split_load_v(u32x4 (&v)[2][2], const PrefillParams& p, const ItemState& st, int db,
+                                             int pg0, int pg1) {
 #pragma unroll
-  for (int db = 0; db < 4; ++db)
+  for (int kk = 0; kk < 2; ++kk) {
+    const uint8_t* vb = p.v_codes + ((int64_t)(kk ? pg1 : pg0) * p.h_kv + st.hk) * (kD * kPage);
 #pragma unroll
     for (int w = 0; w < 2; ++w)
-      v[db][w] = page_load16(vb, kD * kPage, st.lc * kPage + 32 * st.hf, 32 * db * kPage + 16 * w);
-}
-
-// nvalid: keys of these 64 before kv_len (bytes past them are cleared)
-__device__ __forceinline__ void split_pv(u32x4 (&v)[4][2], const i32x8& pb, f32x16 (&o)[4], const ItemState& st,
-                                         int nvalid) {
-  if (nvalid < kPage) {   // uniform: the sequence's last keys
-#pragma unroll
-    for (int db = 0; db < 4; ++db)
-#pragma unroll
-      for (int w = 0; w < 2; ++w) v[db][w] = zero_tail(v[db][w], nvalid - 32 * st.hf - 16 * w);
-  }
-#pragma unroll
-  for (int db = 0; db < 4; ++db) {
-    const i32x8 vop = {(int)v[db][0][0], (int)v[db][0][1], (int)v[db][0][2], (int)v[db][0][3],
-                       (int)v[db][1][0], (int)v[db][1][1], (int)v[db][1][2], (int)v[db][1][3]};
-    o[db] = mfma32_fp8(vop, pb, o[db]);
+      v[kk][w] = page_load16(vb, kD * kPage, st.lc * kPage + 32 * st.hf, 32 * db * kPage + 16 * w);
   }
 }
 
 template <bool SMOOTH, bool MX>
 __device__ __forceinline__ void prefill_split_item(const PrefillParams& p, int b, int h, int r0, SplitSmem& sm) {
   ItemState st;
-  item_setup<MX, kSplitWaves, true>(p, b, h, r0, st);
+  item_setup<MX>(p, b, h, r0, kWaveRows, r0, st);
   const int wave = __builtin_amdgcn_readfirstlane(st.wave);
+  const bool pv_wave = wave < kPvWaves;
   const int32_t* ptab = p.page_table + (int64_t)st.b * p.max_pages;
   const int npg = (st.kvl + 63) >> 6;
-  auto page = [&](int i) { return ptab[min(max(i, 0), npg - 1)]; };
+  // the 16 pages of tile group q (tiles 8q .. 8q + 7), one per lane, clamped to
+  // mapped ones for tiles outside the sequence, whose data is not used
+  auto window = [&](int q) { return ptab[min(max(16 * q + (st.lane & 15), 0), npg - 1)]; };
 
-  f32x16 o[4];
-#pragma unroll
-  for (int db = 0; db < 4; ++db) o[db] = (f32x16){};
-  SoftState ss = {-INFINITY, 0.0f, 0.0f};   // m: running maximum after this wave's latest tile
+  f32x16 o = {};                            // waves 0 .. 3: O^T of their channels
+  float l = 0.0f;                           // and this lane's share of the row sum
   float mround = -INFINITY;                 // running maximum after all tiles of the earlier rounds
+  SoftState ss;
   f32x16 s[4];
   PTile pt;
   SplitK k;
-  u32x4 v[4][2];
+  constexpr int kAheadV = 4;                // V tiles in flight
+  // MXFP4: K and V are loaded as soon as their registers are free (512 rows behind
+  // 32000 tokens, 32:8: 270 -> 261 us).  NVFP4 has 32 query and 4 scale registers
+  // more and spills so (379 us against 325); it loads K and the last two V tiles
+  // after the first PV products.
+  constexpr bool kEarly = MX;
+  u32x4 v[kAheadV][2][2];
+
+  // V of tile t (of eight, last first) of the tile group whose pages are in win
+  auto load_v = [&](int t, int win) {
+    split_load_v(v[t % kAheadV], p, st, wave, __builtin_amdgcn_readlane(win, 2 * (7 - t)),
+                 __builtin_amdgcn_readlane(win, 2 * (7 - t) + 1));
+  };
+  // PV of tile t of tile group q, whose P is in buffer buf
+  auto pv = [&](int t, int buf, int q) {
+    const float alpha = sm.alpha[buf][t][st.lc];
+    l = __builtin_fmaf(alpha, l, sm.ps[buf][t][st.lane]);
+    if (__builtin_amdgcn_ballot_w64(alpha != 1.0f) != 0) o *= alpha;
+    u32x4 (&vt)[2][2] = v[t % kAheadV];
+    const int nvalid = st.kvl - (8 * q + 7 - t) * kTile;   // keys of the tile before kv_len
+    if (nvalid < kTile) {   // uniform: the sequence's last keys
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+        for (int w = 0; w < 2; ++w) vt[kk][w] = zero_tail(vt[kk][w], nvalid - 64 * kk - 32 * st.hf - 16 * w);
+    }
+#pragma unroll
+    for (int kk = 0; kk < 2; ++kk) {
+      const u32x4 pa = sm.p[buf][t][2 * kk][st.lane], pc = sm.p[buf][t][2 * kk + 1][st.lane];
+      const i32x8 vop = {(int)vt[kk][0][0], (int)vt[kk][0][1], (int)vt[kk][0][2], (int)vt[kk][0][3],
+                         (int)vt[kk][1][0], (int)vt[kk][1][1], (int)vt[kk][1][2], (int)vt[kk][1][3]};
+      const i32x8 pop = {(int)pa[0], (int)pa[1], (int)pa[2], (int)pa[3], (int)pc[0], (int)pc[1], (int)pc[2], (int)pc[3]};
+      o = mfma32_fp8(vop, pop, o);
+    }
+  };
 
   const int rounds = (st.j_hi >> 3) + 1;
-  int j = 8 * (rounds - 1) + 7 - wave;      // this wave's tile of the round
-  int c0 = __builtin_amdgcn_readfirstlane(page(2 * j)), c1 = __builtin_amdgcn_readfirstlane(page(2 * j + 1));
-  int n0 = page(2 * (j - 8)), n1 = page(2 * (j - 8) + 1);   // the next round's pages
-  split_load_k<MX, SMOOTH>(k, p, st, c0, c1);
-  for (int r = 0; r < rounds; ++r, j -= 8) {
+  int q = rounds - 1;                       // tile group of the round; this wave's tile is 8q + 7 - wave
+  const int e0 = 2 * (kSplitWaves - 1 - wave);
+  int wprev = 0, wcur = window(q), wnext = window(q - 1);
+  split_load_k<MX, SMOOTH>(k, p, st, __builtin_amdgcn_readlane(wcur, e0), __builtin_amdgcn_readlane(wcur, e0 + 1));
+  auto load_next_k = [&]() {
+    split_load_k<MX, SMOOTH>(k, p, st, __builtin_amdgcn_readlane(wnext, e0), __builtin_amdgcn_readlane(wnext, e0 + 1));
+  };
+  for (int r = 0; r < rounds; ++r, --q) {
+    const bool have_pv = pv_wave && r > 0;
+    const int key0 = (8 * q + kSplitWaves - 1 - wave) * kTile;
+    if (have_pv) {
+#pragma unroll
+      for (int t = 0; t < kAheadV; ++t) load_v(t, wprev);
+    }
+    __builtin_amdgcn_sched_barrier(0);
     // A tile past the row block (first round only) reads mapped pages, is masked
     // whole and adds nothing.
     split_qk<MX, SMOOTH>(s, k, st);
     __builtin_amdgcn_sched_barrier(0);
-    split_load_v(v, p, st, c0);
-    if (j * kTile + kTile - 1 > st.wpos_min) mask_tile(s, j * kTile, st);
+    if (kEarly) load_next_k();
+    if (key0 + kTile - 1 > st.wpos_min) mask_tile(s, key0, st);
     float mxa = -INFINITY, mxb = -INFINITY;
 #pragma unroll
     for (int kb = 0; kb < 4; kb += 2)
@@ -161,77 +209,74 @@ __device__ __forceinline__ void prefill_split_item(const PrefillParams& p, int b
       }
     const float mx = wave_max32(fmaxf(mxa, mxb));
     sm.top[r & 1][wave][st.lc] = mx;   // both lane halves hold it
+    // this round's row maxima and the last one's P are there after it; the buffers
+    // of the round before that are free again
     __syncthreads();
-    // running maximum of this wave's tile: the earlier rounds' and the tiles up to it
-    float mine = mround;
+    // running maximum before this wave's tile: the earlier rounds' and the tiles before it
+    ss.m = mround;
 #pragma unroll
     for (int w = 0; w < kSplitWaves; ++w) {
       const float t = sm.top[r & 1][w][st.lc];
       mround = fmaxf(mround, t);
-      if (w <= wave) mine = fmaxf(mine, t);
+      if (w < wave) ss.m = fmaxf(ss.m, t);
     }
-    const float muse = (mine == -INFINITY) ? 0.0f : mine;
+    if (have_pv) {
+#pragma unroll
+      for (int t = 0; t < kAheadV; ++t) {
+        pv(t, (r - 1) & 1, q + 1);
+        if (kEarly || t < 2) load_v(t + kAheadV, wprev);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (!kEarly) load_next_k();
+    __builtin_amdgcn_sched_barrier(0);
+    const float mnew = fmaxf(ss.m, mx);
+    const float muse = (mnew == -INFINITY) ? 0.0f : mnew;
     const float alpha = (ss.m == -INFINITY) ? 0.0f : __builtin_amdgcn_exp2f((ss.m - muse) * st.lam2);
-    ss.m = mine;
     ss.bias = __builtin_fmaf(-muse, st.lam2, kLog2PScale<kPvFp8>);
-    rescale(o, alpha);
     float ps = 0.0f;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
       ps += exp_block<kPvFp8, 0>(s[kb], kb, st, ss, pt);
       __builtin_amdgcn_sched_barrier(0);
     }
-    ss.l = alpha * ss.l + ps;
-    const int key0 = j * kTile;
-    split_pv(v, pt.pb[0], o, st, st.kvl - key0);
-    __builtin_amdgcn_sched_barrier(0);
-    split_load_v(v, p, st, c1);
-    c0 = __builtin_amdgcn_readfirstlane(n0);
-    c1 = __builtin_amdgcn_readfirstlane(n1);
-    split_load_k<MX, SMOOTH>(k, p, st, c0, c1);
-    n0 = page(2 * (j - 16));
-    n1 = page(2 * (j - 16) + 1);
-    __builtin_amdgcn_sched_barrier(0);
-    split_pv(v, pt.pb[1], o, st, st.kvl - key0 - kPage);
+    if (!kEarly && have_pv) {
+      load_v(6, wprev);
+      load_v(7, wprev);
+    }
+    sm.alpha[r & 1][wave][st.lc] = alpha;
+    sm.ps[r & 1][wave][st.lane] = ps;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const i32x8& x = pt.pb[i >> 1];
+      const int f = 4 * (i & 1);
+      sm.p[r & 1][wave][i][st.lane] = (u32x4){(uint32_t)x[f], (uint32_t)x[f + 1], (uint32_t)x[f + 2], (uint32_t)x[f + 3]};
+    }
+    if (have_pv) {
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = kAheadV; t < kSplitWaves; ++t) pv(t, (r - 1) & 1, q + 1);
+    }
+    wprev = wcur;
+    wcur = wnext;
+    wnext = window(q - 2);
     __builtin_amdgcn_sched_barrier(0);
   }
-
-  // add the waves' states, scaled to the final maximum (mround)
-  const float lt = ss.l + __shfl_xor(ss.l, 32);
+  if (pv_wave) {
 #pragma unroll
-  for (int db = 0; db < 4; ++db) asm volatile("" : "+v"(o[db]));   // full-wave MFMAs (see prefill_item)
-  if (st.lane < 32) {
-    sm.m[wave][st.lc] = ss.m;
-    sm.l[wave][st.lc] = lt;
+    for (int t = 0; t < kAheadV; ++t) load_v(t, wprev);
   }
-#pragma unroll
-  for (int db = 0; db < 4; ++db)
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      *reinterpret_cast<f32x4*>(&sm.o[wave][st.lc * kSplitStride + 32 * db + 8 * i + 4 * st.hf]) =
-          (f32x4){o[db][4 * i], o[db][4 * i + 1], o[db][4 * i + 2], o[db][4 * i + 3]};
   __syncthreads();
+  if (!pv_wave) return;
 #pragma unroll
-  for (int i = 0; i < kWaveRows / kSplitWaves; ++i) {   // four rows per wave, two channels per lane
-    const int row = wave * (kWaveRows / kSplitWaves) + i;
-    float M = -INFINITY, L = 0.0f, a0 = 0.0f, a1 = 0.0f;
-#pragma unroll
-    for (int w = 0; w < kSplitWaves; ++w) M = fmaxf(M, sm.m[w][row]);
-    const float muse = (M == -INFINITY) ? 0.0f : M;
-#pragma unroll
-    for (int w = 0; w < kSplitWaves; ++w) {
-      const float f = __builtin_amdgcn_exp2f((sm.m[w][row] - muse) * st.lam2);
-      const float2 ov = *reinterpret_cast<const float2*>(&sm.o[w][row * kSplitStride + 2 * st.lane]);
-      L = __builtin_fmaf(f, sm.l[w][row], L);
-      a0 = __builtin_fmaf(f, ov.x, a0);
-      a1 = __builtin_fmaf(f, ov.y, a1);
-    }
-    if (st.wrow0 + row < st.nq) {
-      const float inv = __frcp_rn(L);
-      *reinterpret_cast<uint32_t*>(p.out + ((int64_t)(st.q0 + st.wrow0 + row) * p.h_q + st.h) * kD + 2 * st.lane) =
-          (uint32_t)bf16_rne(a0 * inv) | ((uint32_t)bf16_rne(a1 * inv) << 16);
-    }
+  for (int t = 0; t < kSplitWaves; ++t) {
+    pv(t, (rounds - 1) & 1, 0);
+    if (t + kAheadV < kSplitWaves) load_v(t + kAheadV, wprev);
   }
+  asm volatile("" : "+v"(o));   // full-wave MFMAs (see prefill_item)
+  const float lt = l + __shfl_xor(l, 32);
+  const int row = st.wrow0 + st.lc;
+  if (row < st.nq) store_channels(p, st, row, wave, __frcp_rn(lt), o);
 }
 
 // A call with few row blocks (PrefillParams::few): one workgroup per 32 query
