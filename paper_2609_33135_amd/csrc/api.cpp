@@ -120,9 +120,7 @@ mpfa_status check_decode(const mpfa_decode_args* a, hipStream_t s) {
 
 }  // namespace
 
-// Flags that keep the 256-row kernel at every size.  MPFA_SEED_MFMA is not one of
-// them for the 32-row workgroups: their seed is formed that way for either flag, so
-// the two placements give the same bytes there too.
+// Flags that keep the 256-row kernel at every size.
 constexpr uint32_t kWholeOnly = MPFA_SEED_ELEMWISE | MPFA_PV_BF16 | MPFA_PV_NVFP4;
 
 // Whether a call may gain from 32-row workgroups (prefill_few_block, which decides

@@ -37,13 +37,13 @@ namespace {
 // separate calls either way).
 template <bool SMOOTH, bool MX, bool FEW>
 __global__ __launch_bounds__(512, 1) void mixed_kernel(MixedParams m) {
-  __shared__ __attribute__((aligned(16))) std::conditional_t<FEW, FewSmem<SMOOTH, MX>, PrefillSmemT<MX, kPvFp8>> lds;
+  __shared__ __attribute__((aligned(16))) std::conditional_t<FEW, FewSmem<MX>, PrefillSmemT<MX, kPvFp8>> lds;
   const int i = blockIdx.x;
   if (i < m.first) {
     if (i >= m.n_pre_blocks) return;
-    const int bid = i;
-    if constexpr (FEW) prefill_few_block<SMOOTH, MX>(m.pre, bid, lds);
-    else prefill_block<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8, kItemWaves>(m.pre, bid, lds);
+    constexpr int kSeed = SMOOTH ? kSeedInit : kSeedNone;
+    if constexpr (FEW) prefill_few_block<kSeed, MX>(m.pre, i, lds);
+    else prefill_block<kSeed, MX, kPvFp8, kItemWaves>(m.pre, i, lds);
     return;
   }
   // decode group: wave w takes item 8 * group + w = ((b * h_kv + hk) *

@@ -44,10 +44,10 @@ __global__ __launch_bounds__(kThreads / 2, 1) void prefill_half_kernel(PrefillPa
   prefill_block<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8, kItemWaves / 2>(p, blockIdx.x, smem);
 }
 
-template <bool SMOOTH, bool MX>
+template <int SEED, bool MX>
 __global__ __launch_bounds__(kThreads, 1) void prefill_few_kernel(PrefillParams p) {
-  __shared__ __attribute__((aligned(16))) FewSmem<SMOOTH, MX> sm;
-  prefill_few_block<SMOOTH, MX>(p, blockIdx.x, sm);
+  __shared__ __attribute__((aligned(16))) FewSmem<MX> sm;
+  prefill_few_block<SEED, MX>(p, blockIdx.x, sm);
 }
 
 #ifdef MPFA_ABLATION_BUILD
@@ -94,11 +94,13 @@ hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream) {
     }
   } else if (p.few) {
     if (p.mx) {
-      if (p.smooth) prefill_few_kernel<true, true><<<grid, block, 0, stream>>>(p);
-      else prefill_few_kernel<false, true><<<grid, block, 0, stream>>>(p);
+      if (!p.smooth) prefill_few_kernel<kSeedNone, true><<<grid, block, 0, stream>>>(p);
+      else if (p.seed_mfma) prefill_few_kernel<kSeedMfma, true><<<grid, block, 0, stream>>>(p);
+      else prefill_few_kernel<kSeedInit, true><<<grid, block, 0, stream>>>(p);
     } else {
-      if (p.smooth) prefill_few_kernel<true, false><<<grid, block, 0, stream>>>(p);
-      else prefill_few_kernel<false, false><<<grid, block, 0, stream>>>(p);
+      if (!p.smooth) prefill_few_kernel<kSeedNone, false><<<grid, block, 0, stream>>>(p);
+      else if (p.seed_mfma) prefill_few_kernel<kSeedMfma, false><<<grid, block, 0, stream>>>(p);
+      else prefill_few_kernel<kSeedInit, false><<<grid, block, 0, stream>>>(p);
     }
   } else if (p.pv == kPvBf16) {
     if (!p.smooth) prefill_kernel<kSeedNone, false, kPvBf16><<<grid, block, 0, stream>>>(p);

@@ -290,7 +290,7 @@ __device__ __forceinline__ void prefill_split_item(const PrefillParams& p, int b
 // 102, 256 behind 16000 8:2 355 / 80, 1000-token prompt 8:2 33 / 14.5, 1024
 // behind 16000 32:8 377 / 341; not split: 2048 behind 16000 430 (split 696),
 // 2048-token prompt 57 (124), 250-token prompt 16.1 (17).
-template <bool SMOOTH, bool MX>
+template <bool MX>
 struct FewSmem {
   union {
     SplitSmem split;
@@ -298,8 +298,8 @@ struct FewSmem {
   };
 };
 
-template <bool SMOOTH, bool MX>
-__device__ __forceinline__ void prefill_few_block(const PrefillParams& p, int bid, FewSmem<SMOOTH, MX>& sm) {
+template <int SEED, bool MX>
+__device__ __forceinline__ void prefill_few_block(const PrefillParams& p, int bid, FewSmem<MX>& sm) {
   int b, h, rank;
   map_item(p, bid, b, h, rank);
   const int blk = p.n_qtiles - 1 - rank;   // 32-row block
@@ -312,12 +312,12 @@ __device__ __forceinline__ void prefill_few_block(const PrefillParams& p, int bi
   const float start = (float)p.q_start[b], rows = (float)nq;
   const float most = (start + rows) * (1.0f / kTile), mean = (start + 0.5f * rows) * (1.0f / kTile);
   if (4.0f + (float)per_cu * (7.5f + 0.625f * mean) < 5.0f + (MX ? 2.0f : 2.65f) * most) {
-    prefill_split_item<SMOOTH, MX>(p, b, h, blk * kWaveRows, sm.split);
+    prefill_split_item<SEED != kSeedNone, MX>(p, b, h, blk * kWaveRows, sm.split);
     return;
   }
   const int item = blk / kItemWaves, last = min((item + 1) * kItemWaves, (nq + kWaveRows - 1) / kWaveRows) - 1;
   if (blk == last)   // the first of the eight in dispatch order
-    prefill_item<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8, kItemWaves>(p, b, h, item * kItemRows, sm.item);
+    prefill_item<SEED, MX, kPvFp8, kItemWaves>(p, b, h, item * kItemRows, sm.item);
 }
 
 }  // namespace

@@ -106,11 +106,18 @@ def test_prefill_deterministic(orc, mp):
     assert np.array_equal(a, b)
 
 
-def test_prefill_seed_modes_bit_identical(orc, mp):
+# 700 + 45 rows of 8:2 heads run as 32-row items, which form the seed by MFMA for
+# either flag; 45 + 200 of 32:8 in 128-row workgroups against 256-row ones; the ragged
+# batch and the 2100 rows are past the limits of both, so each placement runs its own
+# 256-row kernel
+@pytest.mark.parametrize("mx", [False, True])
+@pytest.mark.parametrize("seqlens,h_q,h_kv", [([700, 45], 8, 2), ([45, 200], 32, 8), ([1, 130, 300, 513], 32, 8),
+                                              ([2100], 32, 8)])
+def test_prefill_seed_modes_bit_identical(orc, mp, seqlens, h_q, h_kv, mx):
     """The rank-one BF16 MFMA seed and the accumulator-input seed give the same
     FP32 accumulator start (the BF16 Delta_S value), hence identical outputs."""
-    print("case: seed modes", flush=True)
-    run = H.Run(orc, mp, 29, [700, 45], 8, 2)
+    print(f"case: seed modes {seqlens} {h_q}:{h_kv} mx={mx}", flush=True)
+    run = H.Run(orc, mp, 29, seqlens, h_q, h_kv, mxfp4=mx)
     a = run.prefill_gpu()
     b = run.prefill_gpu(extra_flags=mp.SEED_MFMA)
     assert np.array_equal(a, b)
@@ -133,12 +140,13 @@ def test_prefill_elementwise_placement(orc, mp, mx):
         assert np.array_equal(run.prefill_gpu(extra_flags=mp.SEED_ELEMWISE), out)
 
 
-def test_prefill_repeatable_all_modes(orc, mp):
+@pytest.mark.parametrize("h_q,h_kv", [(8, 2), (32, 8)])   # 32-row workgroups, 256-row ones
+def test_prefill_repeatable_all_modes(orc, mp, h_q, h_kv):
     """Every seed mode gives bit-identical outputs over repeated launches (a
     missing synchronisation or an unsatisfied hardware hazard shows up as
     run-to-run differences), and the two placements of the compensation agree."""
     print("case: repeatability", flush=True)
-    run = H.Run(orc, mp, 17, [1, 130, 300, 513], 8, 2, outliers=True, smooth=True)
+    run = H.Run(orc, mp, 17, [1, 130, 300, 513], h_q, h_kv, outliers=True, smooth=True)
     first = {}
     for _ in range(12):
         for fl in (0, mp.SEED_MFMA):
@@ -148,20 +156,21 @@ def test_prefill_repeatable_all_modes(orc, mp):
             else:
                 first[fl] = out
     assert np.array_equal(first[0], first[mp.SEED_MFMA])
-    direct = H.Run(orc, mp, 17, [1, 130, 300, 513], 8, 2, outliers=True, smooth=False)
+    direct = H.Run(orc, mp, 17, [1, 130, 300, 513], h_q, h_kv, outliers=True, smooth=False)
     a = direct.prefill_gpu()
     for _ in range(6):
         assert np.array_equal(direct.prefill_gpu(), a)
 
 
+@pytest.mark.parametrize("h_q,h_kv", [(8, 2), (32, 8)])   # 32-row workgroups, 256-row ones
 @pytest.mark.parametrize("smooth", [True, False])
-def test_prefill_mxfp4_ragged(orc, mp, smooth):
+def test_prefill_mxfp4_ragged(orc, mp, smooth, h_q, h_kv):
     """MXFP4 variant over a ragged GQA batch, every output row."""
-    print(f"case: mxfp4 prefill smooth={smooth}", flush=True)
+    print(f"case: mxfp4 prefill smooth={smooth} {h_q}:{h_kv}", flush=True)
     seqlens = [1, 130, 300, 513]
-    run = H.Run(orc, mp, 19, seqlens, 8, 2, outliers=True, smooth=smooth, mxfp4=True)
+    run = H.Run(orc, mp, 19, seqlens, h_q, h_kv, outliers=True, smooth=smooth, mxfp4=True)
     out = run.prefill_gpu()
-    _check(run, out, _all_items(seqlens, 8), label=f"mxfp4 smooth={smooth}")
+    _check(run, out, _all_items(seqlens, h_q), label=f"mxfp4 smooth={smooth}")
     if smooth:
         assert np.array_equal(out, run.prefill_gpu(extra_flags=mp.SEED_MFMA))
     for _ in range(4):

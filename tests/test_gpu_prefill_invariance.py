@@ -45,7 +45,8 @@ def test_chunks_and_wide_tables(orc, mp, h_q, h_kv, total, mxfp4):  # noqa: F811
     run = H.Run(orc, mp, 96, [total], h_q, h_kv, mxfp4=mxfp4, stale_fill=True)
     whole = _bits(run, [total], flags)[0]
     for pages in (64, 2048):
-        assert np.array_equal(_bits(run, [total], flags, pages)[0], whole), pages
+        for seed in (0, mp.SEED_MFMA):   # a wide table's whole items form the seed as the flag says
+            assert np.array_equal(_bits(run, [total], flags | seed, pages)[0], whole), (pages, seed)
     for rows in (1, 40, 300):
         assert np.array_equal(_bits(run, [rows], flags)[0], whole[-rows:]), rows
         assert np.array_equal(_bits(run, [rows], flags, 2048)[0], whole[-rows:]), rows
