@@ -397,11 +397,16 @@ __device__ __forceinline__ void qk_block(f32x16& s, int kb, const PrefillSmemT<M
   }
 }
 
-// P operands of the PV product of one tile: FP8 words (kPvFp8) or eight
-// BF16 / exact FP16 values per MFMA (kPvBf16, kPvNvfp4).
+// P operands of the PV product of one tile: FP8 words (kPvFp8), eight BF16 values
+// per MFMA (kPvBf16), or their E2M1 codes and the scales of 16 keys (kPvNvfp4),
+// made exact FP16 next to the MFMA: held as such from the softmax on they are 20
+// registers more, and the pipelined step spilled 29 (131072 tokens, 40:8: 263 ms
+// so, 212.5 with the codes and no spill).
 struct PTile {
   i32x8 pb[2];     // keys 64kk + 32hf .. +31
   f16x8 ph[8];     // keys 64(t/4) + 32hf + 8(t%4) .. +7
+  uint32_t pc[8];  // the same keys
+  uint32_t psc[4]; // E4M3 scale of codes 2i, 2i + 1
 };
 
 // Softmax state of the wave's query column.
@@ -516,9 +521,11 @@ __device__ __forceinline__ float exp_block(const f32x16& s, int kb, const ItemSt
           cw[w] = fp4_pair(cw[w], div_by_scale(ev[8 * w + 2 * j], sd, r), div_by_scale(ev[8 * w + 2 * j + 1], sd, r),
                            1.0f, j);
     }
-    const ScaleSplit sp = split_e4m3(sc);
-    pt.ph[2 * kb] = dequant8(cw[0], sp);
-    pt.ph[2 * kb + 1] = dequant8(cw[1], sp);
+    uint32_t scale = sc;
+    asm volatile("" : "+v"(cw[0]), "+v"(cw[1]), "+v"(scale), "+v"(ps));   // the codes are formed here (see the FP8 words)
+    pt.pc[2 * kb] = cw[0];
+    pt.pc[2 * kb + 1] = cw[1];
+    pt.psc[kb] = scale;
   }
   return ps;
 }
@@ -554,14 +561,15 @@ __device__ __forceinline__ void pv_tile(const PrefillSmemT<MX, PV>& sm, int buf,
     // those keys) and B (the lane's own P values) pair the same keys
 #pragma unroll
     for (int t = 0; t < 8; ++t) {
+      const f16x8 ph = PV == kPvNvfp4 ? dequant8h(pt.pc[t], e4m3_pair_f16(pt.psc[t >> 1])[0]) : pt.ph[t];
 #pragma unroll
       for (int db = 0; db < 4; ++db) {
         const u32x4 va =
             *reinterpret_cast<const u32x4*>(vp + 32 * db * sm.kVStride + 128 * (t >> 2) + 16 * (t & 3));
         if (PV == kPvBf16)
-          o[db] = mfma32_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, pt.ph[t]), o[db]);
+          o[db] = mfma32_bf16(__builtin_bit_cast(bf16x8, va), __builtin_bit_cast(bf16x8, ph), o[db]);
         else
-          o[db] = mfma32_f16(__builtin_bit_cast(f16x8, va), pt.ph[t], o[db]);
+          o[db] = mfma32_f16(__builtin_bit_cast(f16x8, va), ph, o[db]);
       }
     }
   }
@@ -724,6 +732,7 @@ __device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int 
     if (kLateV) load_v();
     pv_tile<MX, PV>(sm, j & 1, pt, o, st);
     if (kLateV) put_v(j - 1, kTile);
+    if (PV == kPvNvfp4) __builtin_amdgcn_sched_barrier(0);
     alpha = max_tile<PV, ABL>(s, st, ss);
     ps = exp_block<PV, ABL>(s[0], 0, st, ss, pt);
     __syncthreads();
