@@ -21,7 +21,7 @@ namespace {
 
 constexpr int kPrefillRows = 256;   // query rows per prefill workgroup
 constexpr int kFewRows = 32;        // the same for calls with few query rows
-constexpr int kHalfBlocks = 416;    // most workgroups of 128 rows (see prefill_half_kernel)
+constexpr int kHalfBlocks = 416;    // most workgroups of 128 rows (see item_rows, prefill_half_kernel)
 constexpr int kMaxKvHeads = mpfa::kMaxKvHeadsQuant;
 constexpr int kMaxDecodeGroup = 8;  // query heads per KV head packed in one decode wave
 constexpr float kLambda = 0.12751743074173085f;   // log2(e) / sqrt(128)
@@ -139,8 +139,8 @@ static bool prefill_few(const mpfa_prefill_args* a) {
 }
 
 // Host-side validation of the prefill arguments and their launch parameters.
-// may_halve: 128-row workgroups may be chosen (not in the mixed step's grid of
-// 512-thread ones).
+// may_halve: items of 128 rows may be chosen (not in the mixed step, whose decode
+// groups would share the units they take).
 static mpfa_status prefill_params(const mpfa_prefill_args* a, mpfa::PrefillParams& p, bool may_halve) {
   if (!a) return MPFA_ERR_INVALID;
   if (a->head_dim != MPFA_HEAD_DIM) return a->head_dim > 0 ? MPFA_ERR_UNSUPPORTED : MPFA_ERR_INVALID;
@@ -173,9 +173,11 @@ static mpfa_status prefill_params(const mpfa_prefill_args* a, mpfa::PrefillParam
             n_qtiles * a->h_q * (int64_t)a->batch > mpfa::kComputeUnits;
   p.few = prefill_few(a);
   const int64_t halves = ((int64_t)a->max_seqlen_q + kPrefillRows / 2 - 1) / (kPrefillRows / 2);
-  p.half = may_halve && !p.few && !p.order && halves > 1 && halves * a->h_q * a->batch <= kHalfBlocks &&
-           !(a->flags & (kWholeOnly | MPFA_SEED_MFMA));
-  p.n_qtiles = p.few ? (a->max_seqlen_q + kFewRows - 1) / kFewRows : (int)(p.half ? halves : n_qtiles);
+  const int64_t half_blocks = halves * a->h_q * a->batch;
+  if (may_halve && !p.order && halves > 1 && half_blocks <= kHalfBlocks &&
+      !(a->flags & (p.few ? kWholeOnly : kWholeOnly | MPFA_SEED_MFMA)))
+    p.half = half_blocks <= mpfa::kComputeUnits ? mpfa::kHalfAll : mpfa::kHalfAsk;
+  p.n_qtiles = (int)(p.few ? 4 * halves : p.half ? halves : n_qtiles);   // few: 32-row blocks, whole groups of four
   p.smooth = smooth;
   p.seed_mfma = (a->flags & MPFA_SEED_MFMA) != 0;
   p.seed_elem = (a->flags & MPFA_SEED_ELEMWISE) != 0;

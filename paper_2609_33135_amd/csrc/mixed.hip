@@ -43,7 +43,7 @@ __global__ __launch_bounds__(512, 1) void mixed_kernel(MixedParams m) {
     if (i >= m.n_pre_blocks) return;
     constexpr int kSeed = SMOOTH ? kSeedInit : kSeedNone;
     if constexpr (FEW) prefill_few_block<kSeed, MX>(m.pre, i, lds);
-    else prefill_block<kSeed, MX, kPvFp8, kItemWaves>(m.pre, i, lds);
+    else prefill_block<kSeed, MX, kPvFp8>(m.pre, i, lds);
     return;
   }
   // decode group: wave w takes item 8 * group + w = ((b * h_kv + hk) *

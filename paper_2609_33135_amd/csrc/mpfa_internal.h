@@ -43,11 +43,15 @@ struct QuantParams {
   int64_t num_pages;
 };
 
+// Items of 128 rows instead of 256: never, where the contexts are such that it pays
+// (item_rows), or always.
+enum HalfMode { kHalfNever = 0, kHalfAsk = 1, kHalfAll = 2 };
+
 struct PrefillParams {
   int batch, h_q, h_kv, max_pages;
   int n_qtiles;     // max query tiles of one sequence (256 rows; 128 with half, 32 with few)
   int order;        // 1: sequences may start apart, dispatch the longest items first
-  int half;         // 1: 128-row workgroups
+  int half;         // HalfMode
   int few;          // 1: few row blocks, one workgroup per 32 rows (see prefill_few_block)
   int smooth;
   int seed_mfma;    // 1: compensation formed by the rank-one BF16 MFMA, 0: accumulator input

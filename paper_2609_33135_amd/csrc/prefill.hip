@@ -30,18 +30,22 @@ constexpr int kThreads = kItemWaves * 64;
 template <int SEED, bool MX, int PV, int ABL = 0>
 __global__ __launch_bounds__(kThreads, 1) void prefill_kernel(PrefillParams p) {
   __shared__ __attribute__((aligned(16))) PrefillSmemT<MX, PV> smem;
-  prefill_block<SEED, MX, PV, kItemWaves, ABL>(p, blockIdx.x, smem);
+  prefill_block<SEED, MX, PV, ABL>(p, blockIdx.x, smem);
 }
 
-// Short prompts: 128 rows and four waves per workgroup, twice the workgroups for
-// a chip that 256-row ones leave half empty, and a shorter tile step (one wave
-// per SIMD).  The same bytes.  Taken up to kHalfBlocks workgroups (api.cpp):
-// 250 tokens 32:8 15.5 -> 12.7 us, 777 27.2 -> 23.4, 1300 (352 workgroups) 38.9 ->
-// 34.4, 1600 (416) 44.8 -> 42.9, but 2048 (512) 57.3 against 59.1.
+// Short prompts: a workgroup per 128 rows, with items of 128 rows where that pays, else
+// every other one takes 256 (item_rows).  The same bytes.  Taken up to kHalfBlocks
+// workgroups (api.cpp): 250 tokens 32:8 16.0 -> 10.8 us, 1600 (416 workgroups) 45 ->
+// 36.3.  Above, one prompt would gain (2048 tokens, 512: 56.4 -> 47.3), short batches
+// lose (4 x 300 tokens 40:8, 480: 25.8 -> 26.6).
 template <bool SMOOTH, bool MX>
-__global__ __launch_bounds__(kThreads / 2, 1) void prefill_half_kernel(PrefillParams p) {
+__global__ __launch_bounds__(kThreads, 1) void prefill_half_kernel(PrefillParams p) {
   __shared__ __attribute__((aligned(16))) PrefillSmemT<MX, kPvFp8> smem;
-  prefill_block<SMOOTH ? kSeedInit : kSeedNone, MX, kPvFp8, kItemWaves / 2>(p, blockIdx.x, smem);
+  int b, h, rank;
+  map_item(p, blockIdx.x, b, h, rank);
+  const int blk = p.n_qtiles - 1 - rank;
+  if (blk * kHalfRows >= p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b]) return;
+  prefill_pick_block<SMOOTH ? kSeedInit : kSeedNone, MX, kHalfRows>(p, b, h, blk, item_rows(p, b), smem);
 }
 
 template <int SEED, bool MX>
@@ -83,14 +87,13 @@ hipError_t launch_prefill(const PrefillParams& p, hipStream_t stream) {
     return hipGetLastError();
   }
 #endif
-  if (p.half) {
-    const dim3 half_block(kThreads / 2);
+  if (p.half && !p.few) {
     if (p.mx) {
-      if (p.smooth) prefill_half_kernel<true, true><<<grid, half_block, 0, stream>>>(p);
-      else prefill_half_kernel<false, true><<<grid, half_block, 0, stream>>>(p);
+      if (p.smooth) prefill_half_kernel<true, true><<<grid, block, 0, stream>>>(p);
+      else prefill_half_kernel<false, true><<<grid, block, 0, stream>>>(p);
     } else {
-      if (p.smooth) prefill_half_kernel<true, false><<<grid, half_block, 0, stream>>>(p);
-      else prefill_half_kernel<false, false><<<grid, half_block, 0, stream>>>(p);
+      if (p.smooth) prefill_half_kernel<true, false><<<grid, block, 0, stream>>>(p);
+      else prefill_half_kernel<false, false><<<grid, block, 0, stream>>>(p);
     }
   } else if (p.few) {
     if (p.mx) {

@@ -11,6 +11,7 @@ namespace {
 constexpr int kWaveRows = 32;                // query rows per wave: the columns of one 32x32 MFMA
 constexpr int kItemWaves = 8;
 constexpr int kItemRows = kItemWaves * kWaveRows;
+constexpr int kHalfRows = kItemRows / 2;
 
 // Precision of the PV product: the method's FP8 (P * 448 and V in E4M3), or
 // the two other assignments compared in Sec. 3.1 / Fig. 3a, BF16 P and V, and
@@ -599,8 +600,8 @@ __device__ __forceinline__ void store_output(const PrefillParams& p, const ItemS
   }
 }
 
-// One prefill work item (query head h, query rows r0 .. r0 + 32 * WAVES - 1 of
-// sequence b) executed by a whole workgroup of 64 * WAVES threads.
+// One prefill work item (query head h, query rows r0 .. r0 + rows - 1 of sequence b)
+// executed by a whole workgroup of eight waves, 32 rows each.
 //
 // What bounds it: the matrix pipe and the softmax's vector work on the same
 // SIMD, and, on long prefills, the card's power (MFMA alone on such operands
@@ -620,10 +621,9 @@ __device__ __forceinline__ void store_output(const PrefillParams& p, const ItemS
 //
 // LDS buffers: K(j-1) and V(j) are read in step j; K(j-2) is stored over K(j)
 // and V(j-1) over V(j+1), both read in step j+1, before its barrier.
-template <int SEED, bool MX, int PV, int WAVES, int ABL = 0>
+template <int SEED, bool MX, int PV, int ABL = 0>
 __device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int h, int r0, PrefillSmemT<MX, PV>& sm,
-                                             int rows = WAVES * kWaveRows) {
-  constexpr int kUnits = 8 / WAVES;   // units of a tile per thread
+                                             int rows = kItemRows) {
   constexpr bool kSmooth = SEED != kSeedNone;
   // BF16 V: its 16 registers per thread are held only across the PV product
   // (across the whole step they spill)
@@ -640,48 +640,29 @@ __device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int 
   const int npg = (st.kvl + 63) >> 6;
   const int wv = __builtin_amdgcn_readfirstlane(st.wave);
   const int i = threadIdx.x & 255;   // unit of the page
-  // the page of tile j that holds unit u of this wave's threads (clamped to a
+  // the page of tile j that holds this wave's units, one per thread (clamped to a
   // mapped one for tiles outside the sequence, whose data is not used)
-  auto half_of = [&](int u) { return WAVES == 8 ? wv >> 2 : u; };
-  auto page = [&](int j, int u) { return ptab[min(max(2 * j + half_of(u), 0), npg - 1)]; };
-  KRegs kr[kUnits];
-  VRegs<PV> vr[kUnits];
+  const int half = wv >> 2;
+  auto page = [&](int j) { return ptab[min(max(2 * j + half, 0), npg - 1)]; };
+  KRegs kr;
+  VRegs<PV> vr;
   // page of the next K tile to load (and, a step later, of its V tile): the
   // index is loaded a step before it is used
-  int pgk[kUnits], pgv[kUnits], pgn[kUnits];
-  auto next_pages = [&](int j) {   // tile j's pages start to load, the ones before become current
-#pragma unroll
-    for (int u = 0; u < kUnits; ++u) {
-      pgv[u] = pgk[u];
-      pgk[u] = __builtin_amdgcn_readfirstlane(pgn[u]);
-      pgn[u] = page(j, u);
-    }
+  int pgk, pgv, pgn;
+  auto next_pages = [&](int j) {   // tile j's page starts to load, the one before becomes current
+    pgv = pgk;
+    pgk = __builtin_amdgcn_readfirstlane(pgn);
+    pgn = page(j);
   };
-  auto load_k = [&]() {
-#pragma unroll
-    for (int u = 0; u < kUnits; ++u) fetch_k<MX, kSmooth>(kr[u], p, pgk[u], st.hk, st.h, i);
-  };
-  auto load_v = [&]() {
-#pragma unroll
-    for (int u = 0; u < kUnits; ++u) fetch_v<PV>(vr[u], p, pgv[u], st.hk, i);
-  };
-  auto put_k = [&](int j) {
-#pragma unroll
-    for (int u = 0; u < kUnits; ++u) store_k<SEED, MX, PV>(sm, j & 1, kr[u], st.seed_scale, half_of(u), i);
-  };
-  auto put_v = [&](int j, int nvalid) {
-#pragma unroll
-    for (int u = 0; u < kUnits; ++u) store_v<MX, PV>(sm, j & 1, vr[u], half_of(u), i, nvalid);
-  };
+  auto load_k = [&]() { fetch_k<MX, kSmooth>(kr, p, pgk, st.hk, st.h, i); };
+  auto load_v = [&]() { fetch_v<PV>(vr, p, pgv, st.hk, i); };
+  auto put_k = [&](int j) { store_k<SEED, MX, PV>(sm, j & 1, kr, st.seed_scale, half, i); };
+  auto put_v = [&](int j, int nvalid) { store_v<MX, PV>(sm, j & 1, vr, half, i, nvalid); };
   const int j_hi = st.j_hi;
-#pragma unroll
-  for (int u = 0; u < kUnits; ++u) {
-    pgk[u] = page(j_hi, u);
-    pgn[u] = page(j_hi - 1, u);
-  }
+  pgk = page(j_hi);
+  pgn = page(j_hi - 1);
   load_k();
-#pragma unroll
-  for (int u = 0; u < kUnits; ++u) pgv[u] = pgk[u];
+  pgv = pgk;
   load_v();
   put_k(j_hi);
   next_pages(j_hi - 2);
@@ -752,15 +733,58 @@ __device__ __forceinline__ void prefill_item(const PrefillParams& p, int b, int 
 }
 
 // The item at position `bid` of the dispatch order (largest row tiles first).
-template <int SEED, bool MX, int PV, int WAVES, int ABL = 0>
+template <int SEED, bool MX, int PV, int ABL = 0>
 __device__ __forceinline__ void prefill_block(const PrefillParams& p, int bid, PrefillSmemT<MX, PV>& sm) {
   int b, h, rank;
   map_item(p, bid, b, h, rank);
   int tile = p.n_qtiles - 1 - rank;
-  if (WAVES == kItemWaves && starts_differ(p) && !longest_item(p, rank * p.batch + b, b, tile)) return;
-  const int r0 = tile * (WAVES * kWaveRows);
+  if (starts_differ(p) && !longest_item(p, rank * p.batch + b, b, tile)) return;
+  const int r0 = tile * kItemRows;
   if (r0 >= p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b]) return;
-  prefill_item<SEED, MX, PV, WAVES, ABL>(p, b, h, r0, sm);
+  prefill_item<SEED, MX, PV, ABL>(p, b, h, r0, sm);
+}
+
+// Rows of the items that sequence b is cut into.  Of 128 rows, four waves compute (one
+// per SIMD) and the other four only move their share of the tiles; such a step takes
+// 1.75 us where one of 256 rows takes 2.9 (MXFP4 1.45, 2.2), so they are the better
+// ones while all of them are resident at once (kHalfAll), and past that (kHalfAsk)
+// while a compute unit's share of the tiles is not much more than the longest of them.
+// 32:8 heads, 128 / 256 rows: 777 tokens 18.8 / 28 us, 777 behind 8000 132 / 203, 1600
+// 36.3 / 45, 1600 behind 500 51.0 / 56.5, 1300 behind 1000 57.6 / 62.0, but 1300 behind
+// 4000 142 / 129, 1600 behind 2000 93 / 90.
+__device__ __forceinline__ int item_rows(const PrefillParams& p, int b) {
+  if (p.half != kHalfAsk) return p.half == kHalfAll ? kHalfRows : kItemRows;
+  int blocks = 0, tiles = 0;   // 128-row blocks of one head over the batch, and the KV tiles they visit
+  for (int i = threadIdx.x & 63; i < p.batch; i += 64) {
+    const int n = (p.cu_seqlens_q[i + 1] - p.cu_seqlens_q[i] + kHalfRows - 1) / kHalfRows;
+    blocks += n;
+    tiles += n * min(p.q_start[i] / kTile, 1 << 20) + n * (n + 1) / 2;
+  }
+  if (wave_sum_all(blocks) * p.h_q <= kComputeUnits) return kHalfRows;
+  const float share = (float)wave_sum_all(tiles) * (float)p.h_q / kComputeUnits;
+  const int longest = (p.q_start[b] + p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b] + kTile - 1) / kTile;
+  return share <= 1.15f * (float)longest ? kHalfRows : kItemRows;
+}
+
+// Block blk of ROWS rows of sequence b, head h, whose items have `rows` rows.  Items of
+// 128 rows are taken by the first block of each; of 256, by the first block of one of
+// their two halves, which of them changes every other item: the workgroups of an XCD are
+// dealt to its four shader engines in turn, and with the working ones eight apart all ran
+// on one of them (6000 rows behind 4000 tokens, 8:2 heads, 513 us; so 228).
+template <int SEED, bool MX, int ROWS>
+__device__ __forceinline__ void prefill_pick_block(const PrefillParams& p, int b, int h, int blk, int rows,
+                                                   PrefillSmemT<MX, kPvFp8>& sm) {
+  constexpr int kPer = kHalfRows / ROWS;
+  if (blk % kPer != 0) return;
+  int item = blk / kPer;
+  if (rows == kItemRows) {
+    const bool second = item & 1;
+    item >>= 1;
+    const bool pick = (item >> 1) & 1;
+    const int nq = p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b];
+    if (second != (pick && item * kItemRows + kHalfRows < nq)) return;
+  }
+  prefill_item<SEED, MX, kPvFp8>(p, b, h, item * rows, sm, rows);
 }
 
 }  // namespace

@@ -281,15 +281,16 @@ __device__ __forceinline__ void prefill_split_item(const PrefillParams& p, int b
 
 // A call with few row blocks (PrefillParams::few): one workgroup per 32 query
 // rows, which either splits their KV tiles over its waves, or, where the context
-// is too short for that to pay, one of each eight takes the 256 rows as a whole.
-// The choice is per sequence, from its context on the device.  Model of the
-// call, in us: whole items, all resident, 5 + 2.65 (MXFP4 2.0) per tile of the
-// longest; split items 4, and 7.5 + 5 per eight tiles each, as many one after
-// the other as there are blocks per compute unit.  Measured, whole items / this
-// kernel: 512 rows behind 32000 tokens 32:8 700 / 319 us, 64 behind 20000 266 /
-// 102, 256 behind 16000 8:2 355 / 80, 1000-token prompt 8:2 33 / 14.5, 1024
-// behind 16000 32:8 377 / 341; not split: 2048 behind 16000 430 (split 696),
-// 2048-token prompt 57 (124), 250-token prompt 16.1 (17).
+// is too short for that to pay, takes the rows of a whole item (prefill_pick_block).
+// The choice is per sequence, from its context on the device.  Model of the call, in
+// us: whole items 5 + 1.75 (MXFP4 1.45) per tile of the longest for 128 rows, 2.65 (2.0)
+// for 256, all resident; split items 4, and 7.5 + 5 per eight tiles each (MXFP4 6.5 +
+// 4), as many one after the other as there are blocks per compute unit.  Measured,
+// 32:8 heads, whole items / split: 512 rows behind 16000 tokens 234 / 170 us, 64 behind
+// 16000 221 / 82, 256 behind 2000 40 / 25, 8:2 heads 1024 behind 16000 239 / 88, 2000
+// tokens 34.9 / 29.7 (MXFP4 28.7 / 23.1); not split: 1024 behind 16000 240 (split 340),
+// 500 behind 2000 43.7 (47.2), 1024-token prompt 22.3 (53.9), 256-token prompt 10.8
+// (17.7).
 template <bool MX>
 struct FewSmem {
   union {
@@ -302,22 +303,25 @@ template <int SEED, bool MX>
 __device__ __forceinline__ void prefill_few_block(const PrefillParams& p, int bid, FewSmem<MX>& sm) {
   int b, h, rank;
   map_item(p, bid, b, h, rank);
-  const int blk = p.n_qtiles - 1 - rank;   // 32-row block
+  // 32-row block: first those that begin 128 rows, the only ones with work where the
+  // tiles are not split
+  const int quads = p.n_qtiles / 4, rest = 4 * quads - 1 - rank;
+  const int blk = rank < quads ? 4 * (quads - 1 - rank) : rest / 3 * 4 + 1 + rest % 3;
   const int nq = p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b];
   if (blk * kWaveRows >= nq) return;
   int blocks = 0;   // 32-row blocks of one head over the batch
   for (int i = threadIdx.x & 63; i < p.batch; i += 64)
     blocks += (p.cu_seqlens_q[i + 1] - p.cu_seqlens_q[i] + kWaveRows - 1) / kWaveRows;
   const int per_cu = (wave_sum_all(blocks) * p.h_q + kComputeUnits - 1) / kComputeUnits;
+  const int item = item_rows(p, b);
+  const float per_tile = item == kHalfRows ? (MX ? 1.45f : 1.75f) : (MX ? 2.0f : 2.65f);
   const float start = (float)p.q_start[b], rows = (float)nq;
   const float most = (start + rows) * (1.0f / kTile), mean = (start + 0.5f * rows) * (1.0f / kTile);
-  if (4.0f + (float)per_cu * (7.5f + 0.625f * mean) < 5.0f + (MX ? 2.0f : 2.65f) * most) {
+  const float split = MX ? 6.5f + 0.5f * mean : 7.5f + 0.625f * mean;
+  if (4.0f + (float)per_cu * split < 5.0f + per_tile * most)
     prefill_split_item<SEED != kSeedNone, MX>(p, b, h, blk * kWaveRows, sm.split);
-    return;
-  }
-  const int item = blk / kItemWaves, last = min((item + 1) * kItemWaves, (nq + kWaveRows - 1) / kWaveRows) - 1;
-  if (blk == last)   // the first of the eight in dispatch order
-    prefill_item<SEED, MX, kPvFp8, kItemWaves>(p, b, h, item * kItemRows, sm.item);
+  else
+    prefill_pick_block<SEED, MX, kWaveRows>(p, b, h, blk, item, sm.item);
 }
 
 }  // namespace
