@@ -170,15 +170,45 @@ __global__ __launch_bounds__(256) void stats_partial_kernel(QuantParams p) {
   }
 }
 
+// Sequence and block of the idx-th block of 2^SHIFT tokens of the call; false past the
+// last.  For the grids of one workgroup per block that the call has: those of (blocks of
+// the longest sequence) x (sequences) are mostly empty in a batch of one long prompt and
+// many short ones, and an empty workgroup costs about 0.3 ns of the chip.
+template <int SHIFT>
+__device__ __forceinline__ bool packed_block(const QuantParams& p, int idx, int& b, int& blk) {
+  const int lane = threadIdx.x & 63;
+  for (int b0 = 0; b0 < p.batch; b0 += 64) {
+    const int i = b0 + lane;
+    const int n = i < p.batch ? (p.cu_seqlens[i + 1] - p.cu_seqlens[i] + (1 << SHIFT) - 1) >> SHIFT : 0;
+    int incl = n;
+    for (int d = 1; d < 64; d <<= 1) {
+      const int up = __shfl_up(incl, d);
+      if (lane >= d) incl += up;
+    }
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    if (idx < total) {
+      const int at = __ffsll((unsigned long long)__ballot(incl > idx)) - 1;
+      b = b0 + at;
+      blk = idx - (__builtin_amdgcn_readlane(incl, at) - __builtin_amdgcn_readlane(n, at));
+      return true;
+    }
+    idx -= total;
+  }
+  return false;
+}
+
 // The same for few blocks: one wave per (head, block, sequence), two channels
 // per lane and 32 tokens in flight.  A block is a serial walk over its tokens,
 // so with too few workgroups to fill the chip its latency counts: 16 lanes a
 // head with 8 channels each spend 20 us on the 4096 vector operations and 8
 // round trips of a block, this shape 2 channels' 1024 and 4 (see launch_quantize
 // for the line between the two).  Per channel the tokens add in the same order.
+template <bool PACKED>
 __global__ __launch_bounds__(64) void stats_partial_wave_kernel(QuantParams p) {
   constexpr int kAhead = 32;
-  const int hh = blockIdx.x, blk = blockIdx.y, b = blockIdx.z, lane = threadIdx.x;
+  const int hh = blockIdx.x, lane = threadIdx.x;
+  int blk = blockIdx.y, b = blockIdx.z;
+  if (PACKED && !packed_block<7>(p, blockIdx.y, b, blk)) return;
   const int64_t t0 = p.cu_seqlens[b];
   const int n = p.cu_seqlens[b + 1] - (int)t0;
   const int nblk = (n + 127) >> 7;
@@ -1023,15 +1053,17 @@ __device__ __forceinline__ void group_tables(const QuantParams& p, GroupSmem& sm
   if (tid >= 128) sm.rcp_sd[tid - 128] = (tid & 0x7F) && (tid & 0x7F) < 0x7F ? __fdiv_rn(1.0f, e4m3_value(tid & 0x7F)) : 0.0f;
 }
 
-template <bool MX>
+template <bool MX, bool PACKED>
 __global__ __launch_bounds__(256) void quantize_group_kernel(QuantParams p) {
   __shared__ GroupSmem sm;
-  const int b = blockIdx.z, tid = threadIdx.x;
+  const int tid = threadIdx.x;
+  int b = blockIdx.z, chunk = blockIdx.x;
+  if (PACKED && !packed_block<6>(p, blockIdx.x, b, chunk)) return;
   const int hk = blockIdx.y % p.h_kv;
   const int parts = (int)gridDim.y == p.h_kv ? kPartAll : 1 << (blockIdx.y / p.h_kv);   // 1 or 3 workgroups a group
   const int64_t t0 = p.cu_seqlens[b];
   const int n = p.cu_seqlens[b + 1] - (int)t0;
-  const int i0 = blockIdx.x * kChunk;
+  const int i0 = chunk * kChunk;
   if (i0 >= n) return;
   const int cnt = min(kChunk, n - i0), grp = p.h_q / p.h_kv;
   group_tables(p, sm, t0 + i0, cnt);
@@ -1175,7 +1207,12 @@ __global__ void convert_kernel(int fmt, const float* x, int64_t n, uint8_t* out)
 //  - a workgroup per part up to kPartGroups head groups, about two per CU: 65
 //    tokens 24.8 -> 19.2 us, 777 tokens 23.8 -> 20.4 us; 16 x 2000 tokens (4128
 //    groups) 206 us in one part against 215 us.
+//  - grids of the blocks that the call has (packed_block) instead of (longest) x
+//    (sequences) where the latter are more than twice as many: 30000 + 31 x 1 tokens
+//    243 -> 201 us, 3000 + 200 x 1 83 -> 59, 60000 + 63 x 1 of 8:2 187 -> 108; up to
+//    kPackedBatch sequences, eight steps of the search.
 constexpr int64_t kWaveStats = 18432, kGroupChunks = 520, kPartGroups = 512;
+constexpr int kPackedGrid = 2, kPackedBatch = 512;
 constexpr int kOnePartTokens = 8;   // so few tokens that the parts cost more than they overlap
 
 hipError_t launch_quantize(const QuantParams& p, hipStream_t stream) {
@@ -1191,12 +1228,17 @@ hipError_t launch_quantize(const QuantParams& p, hipStream_t stream) {
   // chunks and blocks of the call, at most (the sequence lengths are on the device)
   const int64_t blocks = (int64_t)p.total_tokens / 128 + p.batch;
   const int64_t chunks = (int64_t)p.total_tokens / kChunk + p.batch;
+  const bool packed = p.batch <= kPackedBatch;
   if (p.need_partials && p.max_seqlen > 0) {
     const unsigned nb = (p.max_seqlen + 127) / 128;
-    if (blocks * hs <= kWaveStats && p.max_seqlen <= 128 * 65535)
-      stats_partial_wave_kernel<<<dim3(hs, nb, p.batch), dim3(64), 0, stream>>>(p);
-    else
+    if (blocks * hs <= kWaveStats && p.max_seqlen <= 128 * 65535) {
+      if (packed && blocks * kPackedGrid < (int64_t)nb * p.batch)
+        stats_partial_wave_kernel<true><<<dim3(hs, (unsigned)blocks), dim3(64), 0, stream>>>(p);
+      else
+        stats_partial_wave_kernel<false><<<dim3(hs, nb, p.batch), dim3(64), 0, stream>>>(p);
+    } else {
       stats_partial_kernel<<<dim3(nb, p.batch), dim3(256), 0, stream>>>(p);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -1209,9 +1251,16 @@ hipError_t launch_quantize(const QuantParams& p, hipStream_t stream) {
   if (p.total_tokens > 0 && p.max_seqlen > 0) {
     const unsigned nc = (p.max_seqlen + kChunk - 1) / kChunk;
     if (group_ok && chunks <= kGroupChunks) {
-      const dim3 grid(nc, p.h_kv * (chunks * p.h_kv <= kPartGroups ? 3 : 1), p.batch);
-      if (p.mx) quantize_group_kernel<true><<<grid, dim3(256), 0, stream>>>(p);
-      else quantize_group_kernel<false><<<grid, dim3(256), 0, stream>>>(p);
+      const unsigned groups = p.h_kv * (chunks * p.h_kv <= kPartGroups ? 3 : 1);
+      if (packed && chunks * kPackedGrid < (int64_t)nc * p.batch) {
+        const dim3 grid((unsigned)chunks, groups);
+        if (p.mx) quantize_group_kernel<true, true><<<grid, dim3(256), 0, stream>>>(p);
+        else quantize_group_kernel<false, true><<<grid, dim3(256), 0, stream>>>(p);
+      } else {
+        const dim3 grid(nc, groups, p.batch);
+        if (p.mx) quantize_group_kernel<true, false><<<grid, dim3(256), 0, stream>>>(p);
+        else quantize_group_kernel<false, false><<<grid, dim3(256), 0, stream>>>(p);
+      }
     } else {
       const dim3 grid(nc, p.batch);
       const size_t lds = (size_t)(p.h_q + p.h_kv) * (kMeanStride + sizeof(float));

@@ -116,3 +116,37 @@ def test_v_copies(orc, mp, lens, pv):
 def test_limits(orc, mp, lens, h_q, h_kv):
     slots, n_pages = _pages(lens)
     _both(orc, mp, lens, h_q, h_kv, mp.SMOOTH | mp.COMPUTE_STATS, slots, n_pages)
+
+
+# one long sequence among many short ones: grids of the blocks that the call has, with
+# empty sequences and more than one round of 64 sequences in the search for a block
+@pytest.mark.parametrize("lens", [[1] * 70 + [0] * 3 + [700, 130] + [1] * 20, [1, 0, 900, 1, 1, 1], [1500] + [0] * 40])
+def test_skewed_batches(orc, mp, lens):
+    slots, n_pages = _pages(lens)
+    for mode in (mp.SMOOTH, 0, mp.SMOOTH | mp.MXFP4):
+        st = _both(orc, mp, lens, 8, 2, mode | mp.COMPUTE_STATS, slots, n_pages)
+        _both(orc, mp, lens, 8, 2, mode, slots, n_pages, stats=(st.q_mean, st.k_mean, st.k_tscale), seed=6)
+
+
+def test_short_sequences_beside_a_long_one_cost_little(mp):
+    """One token each in 31 more sequences: grids of (blocks of the longest) x (sequences)
+    took 1.26 times as long as the long sequence alone."""
+    took = []
+    for lens in ([30000], [30000] + [1] * 31):
+        T, B = sum(lens), len(lens)
+        q, k, v = (torch.randn((T, h, 128), device="cuda", dtype=torch.bfloat16) for h in (32, 8, 8))
+        cu = torch.tensor(np.concatenate([[0], np.cumsum(lens)]), dtype=torch.int32, device="cuda")
+        slots, n_pages = _pages(lens)
+        args = (q, k, v, cu, torch.from_numpy(slots).cuda(), mp.PagedCache(n_pages, 32, 8), mp.SeqStats(B, 32, 8), mp.QuantQ(T, B, 32),
+                mp.SMOOTH | mp.COMPUTE_STATS, max(lens))
+        start, end = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        times = []
+        for _ in range(8):   # the first is a warm-up
+            start.record()
+            for _ in range(10):
+                mp.quantize_qk(*args)
+            end.record()
+            torch.cuda.synchronize()
+            times.append(start.elapsed_time(end))
+        took.append(float(np.median(times[1:])))
+    assert took[1] <= 1.15 * took[0], took
