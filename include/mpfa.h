@@ -92,7 +92,7 @@ typedef enum {
 #define MPFA_COMPUTE_STATS 2u  /* compute means and K tensor scales from this call's tokens  */
 #define MPFA_TSCALE_UNIT   4u  /* NVFP4 tensor scale fixed to 1 (Eq. 1 without a 2nd level) */
 #define MPFA_SEED_MFMA     8u  /* prefill: form the rank-one term 1 Delta_S^T with one BF16
-                                  MFMA per 16-key block (Delta_S in reduction slot 0, ones
+                                  MFMA per 32-key block (Delta_S in reduction slot 0, ones
                                   in B), the paper's formulation (Sec. 5.2), instead of
                                   loading it as the accumulator input; bit-identical       */
 #define MPFA_SEED_ELEMWISE 32u /* prefill: the placement the rank-one seed replaces (Sec. 3.2,

@@ -229,7 +229,7 @@ __device__ __forceinline__ void decode_partition(const DecodeParams& p, int b, i
   for (int db = 0; db < 8; ++db) o[db] = (f32x4){0.f, 0.f, 0.f, 0.f};
   i32x8 pb = {};
 
-  // O^T += V^T P^T for tile t (P in pb, V in the LDS slab).  Keys past the end
+  // O^T += V^T P^T for tile t (P in pb, V in registers).  Keys past the end
   // of the sequence carry P = 0, but their V bytes may be stale cache contents:
   // they are cleared so that 0 * NaN cannot occur.
   auto pv = [&](int t) {

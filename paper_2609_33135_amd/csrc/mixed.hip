@@ -7,8 +7,9 @@
 // head) counter when its state is written; the last one merges the group's
 // query heads (log-sum-exp, the same arithmetic as the separate merge kernel)
 // and resets the counter, so the step needs no second launch.  A workgroup is
-// 512 threads; a prefill item uses about 105 KB of LDS for its two tile buffers, a
-// group of eight decode items none (their K and V go straight to registers).
+// 512 threads; a prefill item uses 106 KB of LDS for its two tile buffers (MXFP4 59;
+// 72 with the few-row items, whose NVFP4 form has 108 bytes of scratch), a group of eight decode items none (their K and V go
+// straight to registers).
 //
 // Placement: a prefill workgroup holds a whole compute unit (its LDS and all
 // of its registers), so prefill and decode cannot share a unit at the same
@@ -18,7 +19,10 @@
 // 1626 for the two calls; 2048 behind 8000 and 32 x 4000 keys 420 / 485 / 470;
 // 16384-token prompt and 64 x 6000 keys 2251 / 2258 / 2316; the decode first is the
 // better one only for a short prompt beside a long decode (1000 tokens, 16 x
-// 30000 keys: 263 / 253 / 204).
+// 30000 keys: 263 / 253 / 204).  Where the decode is the longer part one launch loses
+// to the two calls: a unit holds one workgroup of eight decode waves and drains (barrier,
+// cache write-back, barrier, perhaps a merge) before the next group starts, where the
+// two four-wave workgroups of decode_kernel refill apart.
 #include <type_traits>
 
 #include "decode_body.h"

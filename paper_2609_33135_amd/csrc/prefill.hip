@@ -56,7 +56,7 @@ __global__ __launch_bounds__(kThreads, 1) void prefill_few_kernel(PrefillParams 
 
 #ifdef MPFA_ABLATION_BUILD
 // Characterization library only: softmax ablation level of the method's
-// kernels (compensation as accumulator input, FP8 PV), see softmax_tile.
+// kernels (compensation as accumulator input, FP8 PV), see max_tile.
 int g_ablation = 0;
 #endif
 

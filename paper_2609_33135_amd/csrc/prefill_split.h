@@ -17,6 +17,8 @@
 //   * a round later wave w < 4 accumulates O of channels 32w .. 32w + 31 over the
 //     eight tiles in that order, the other waves being in their softmax meanwhile
 //     (one such wave per SIMD).
+// prefill_few_kernel spills 13 registers in NVFP4 with the compensation (44 bytes a
+// lane), none without it or in MXFP4.
 // Every FP32 operation has the operands and the order it has in prefill_item, so
 // the bytes are the same whichever of the two a call takes.
 #pragma once

@@ -710,6 +710,56 @@ __device__ __forceinline__ void quant_k_rows(const QuantParams& p, const uint8_t
   }
 }
 
+// V of 16 tokens and two adjacent channels, w[j] both values of token j: FP8 bytes of the
+// channel rows.
+__device__ __forceinline__ void v_fp8_16(const uint32_t (&w)[16], u32x4& r0, u32x4& r1) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const uint32_t* wq = w + 4 * q;
+    uint32_t a = fp8_sat_pair(0u, __uint_as_float(wq[0] << 16), __uint_as_float(wq[1] << 16), false);
+    a = fp8_sat_pair(a, __uint_as_float(wq[2] << 16), __uint_as_float(wq[3] << 16), true);
+    uint32_t c = fp8_sat_pair(0u, __uint_as_float(wq[0] & 0xFFFF0000u), __uint_as_float(wq[1] & 0xFFFF0000u), false);
+    c = fp8_sat_pair(c, __uint_as_float(wq[2] & 0xFFFF0000u), __uint_as_float(wq[3] & 0xFFFF0000u), true);
+    r0[q] = a;
+    r1[q] = c;
+  }
+}
+
+// The characterization copies of the same tokens (qq .. qq + 15 of the page) in channel
+// rows crow, crow + 1: BF16 rows (page_run: all 64 tokens present), or an NVFP4 group.
+__device__ __forceinline__ void v_aux_16(const QuantParams& p, const uint32_t (&w)[16], int64_t crow, int qq,
+                                         bool page_run, const float* rcp_sd) {
+  if (p.pv == 1 && page_run) {   // 16 keys of each channel, 32 bytes
+    uint32_t b0[8], b1[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      b0[j] = (w[2 * j] & 0xFFFFu) | (w[2 * j + 1] << 16);
+      b1[j] = (w[2 * j] >> 16) | (w[2 * j + 1] & 0xFFFF0000u);
+    }
+    uint16_t* a16 = reinterpret_cast<uint16_t*>(p.v_aux) + crow * kPage + qq;
+    *reinterpret_cast<u32x4*>(a16) = (u32x4){b0[0], b0[1], b0[2], b0[3]};
+    *reinterpret_cast<u32x4*>(a16 + 8) = (u32x4){b0[4], b0[5], b0[6], b0[7]};
+    *reinterpret_cast<u32x4*>(a16 + kPage) = (u32x4){b1[0], b1[1], b1[2], b1[3]};
+    *reinterpret_cast<u32x4*>(a16 + kPage + 8) = (u32x4){b1[4], b1[5], b1[6], b1[7]};
+  }
+  if (p.pv == 2) {   // one NVFP4 group per channel: these 16 keys (absent ones zero)
+    const int64_t aux_scales = p.num_pages * p.h_kv * kD * 32;   // scale plane offset
+    float x0[16], x1[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+      x0[j] = __uint_as_float(w[j] << 16);
+      x1[j] = __uint_as_float(w[j] & 0xFFFF0000u);
+    }
+    uint32_t sc0, sc1;
+    const uint64_t c0 = nvfp4_group(x0, 1.0f, rcp_sd, &sc0);
+    const uint64_t c1 = nvfp4_group(x1, 1.0f, rcp_sd, &sc1);
+    *reinterpret_cast<uint64_t*>(p.v_aux + crow * 32 + qq / 2) = c0;
+    *reinterpret_cast<uint64_t*>(p.v_aux + (crow + 1) * 32 + qq / 2) = c1;
+    p.v_aux[aux_scales + crow * 4 + qq / 16] = (uint8_t)sc0;
+    p.v_aux[aux_scales + (crow + 1) * 4 + qq / 16] = (uint8_t)sc1;
+  }
+}
+
 template <bool MX>
 __global__ __launch_bounds__(256) void quantize_kernel(QuantParams p) {
   __shared__ int page_start;   // 1: the chunk's tokens are slots 0, 1, ... of one page, in order
@@ -763,7 +813,6 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams p) {
   const bool page_run = page_start && cnt == kChunk;   // whole page rows can be written
   if (page_run || (p.pv == 2 && page_start)) {
     const int64_t page = p.slot_mapping[tok0] / kPage;
-    const int64_t aux_scales = p.num_pages * p.h_kv * kD * 32;   // NVFP4 scale plane offset
     for (int u = tid; u < p.h_kv * (kD / 2); u += blockDim.x) {
       const int h = u / (kD / 2), cp = u % (kD / 2);
       const uint32_t* src = reinterpret_cast<const uint32_t*>(p.v + (tok0 * p.h_kv + h) * kD) + cp;
@@ -780,49 +829,8 @@ __global__ __launch_bounds__(256) void quantize_kernel(QuantParams p) {
         uint32_t w[16];
 #pragma unroll
         for (int j = 0; j < 16; ++j) w[j] = qq + j < cnt ? src[(int64_t)(qq + j) * tstride] : 0u;
-        if (page_run) {
-          u32x4 r0, r1;   // bytes of channels 2cp and 2cp+1
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const uint32_t* wq = w + 4 * q;
-            uint32_t a = fp8_sat_pair(0u, __uint_as_float(wq[0] << 16), __uint_as_float(wq[1] << 16), false);
-            a = fp8_sat_pair(a, __uint_as_float(wq[2] << 16), __uint_as_float(wq[3] << 16), true);
-            uint32_t c = fp8_sat_pair(0u, __uint_as_float(wq[0] & 0xFFFF0000u), __uint_as_float(wq[1] & 0xFFFF0000u), false);
-            c = fp8_sat_pair(c, __uint_as_float(wq[2] & 0xFFFF0000u), __uint_as_float(wq[3] & 0xFFFF0000u), true);
-            r0[q] = a;
-            r1[q] = c;
-          }
-          r0s[qq / 16] = r0;
-          r1s[qq / 16] = r1;
-          if (p.pv == 1) {   // BF16 rows: 16 keys of each channel, 32 bytes
-            uint32_t b0[8], b1[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-              b0[j] = (w[2 * j] & 0xFFFFu) | (w[2 * j + 1] << 16);
-              b1[j] = (w[2 * j] >> 16) | (w[2 * j + 1] & 0xFFFF0000u);
-            }
-            uint16_t* a16 = reinterpret_cast<uint16_t*>(p.v_aux) + crow * kPage + qq;
-            *reinterpret_cast<u32x4*>(a16) = (u32x4){b0[0], b0[1], b0[2], b0[3]};
-            *reinterpret_cast<u32x4*>(a16 + 8) = (u32x4){b0[4], b0[5], b0[6], b0[7]};
-            *reinterpret_cast<u32x4*>(a16 + kPage) = (u32x4){b1[0], b1[1], b1[2], b1[3]};
-            *reinterpret_cast<u32x4*>(a16 + kPage + 8) = (u32x4){b1[4], b1[5], b1[6], b1[7]};
-          }
-        }
-        if (p.pv == 2) {   // one NVFP4 group per channel: these 16 keys (absent ones zero)
-          float x0[16], x1[16];
-#pragma unroll
-          for (int j = 0; j < 16; ++j) {
-            x0[j] = __uint_as_float(w[j] << 16);
-            x1[j] = __uint_as_float(w[j] & 0xFFFF0000u);
-          }
-          uint32_t sc0, sc1;
-          const uint64_t c0 = nvfp4_group(x0, 1.0f, rcp_sd, &sc0);
-          const uint64_t c1 = nvfp4_group(x1, 1.0f, rcp_sd, &sc1);
-          *reinterpret_cast<uint64_t*>(p.v_aux + crow * 32 + qq / 2) = c0;
-          *reinterpret_cast<uint64_t*>(p.v_aux + (crow + 1) * 32 + qq / 2) = c1;
-          p.v_aux[aux_scales + crow * 4 + qq / 16] = (uint8_t)sc0;
-          p.v_aux[aux_scales + (crow + 1) * 4 + qq / 16] = (uint8_t)sc1;
-        }
+        if (page_run) v_fp8_16(w, r0s[qq / 16], r1s[qq / 16]);
+        v_aux_16(p, w, crow, qq, page_run, rcp_sd);
       }
       if (page_run) {
 #pragma unroll
@@ -876,53 +884,16 @@ __device__ __forceinline__ void quant_v_part(const QuantParams& p, int64_t tok0,
   const uint32_t* src = reinterpret_cast<const uint32_t*>(p.v + (tok0 * p.h_kv + h) * kD) + cp;
   const int64_t tstride = (int64_t)p.h_kv * (kD / 2);
   const int64_t crow = (page * p.h_kv + h) * kD + 2 * cp;   // channel row 2cp; 2cp+1 follows
-  const int64_t aux_scales = p.num_pages * p.h_kv * kD * 32;   // NVFP4 scale plane offset
   uint32_t w[16];
 #pragma unroll
   for (int j = 0; j < 16; ++j) w[j] = qq + j < cnt ? src[(int64_t)(qq + j) * tstride] : 0u;
   if (page_run) {
-    u32x4 r0, r1;   // bytes of channels 2cp and 2cp+1
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const uint32_t* wq = w + 4 * q;
-      uint32_t a = fp8_sat_pair(0u, __uint_as_float(wq[0] << 16), __uint_as_float(wq[1] << 16), false);
-      a = fp8_sat_pair(a, __uint_as_float(wq[2] << 16), __uint_as_float(wq[3] << 16), true);
-      uint32_t c = fp8_sat_pair(0u, __uint_as_float(wq[0] & 0xFFFF0000u), __uint_as_float(wq[1] & 0xFFFF0000u), false);
-      c = fp8_sat_pair(c, __uint_as_float(wq[2] & 0xFFFF0000u), __uint_as_float(wq[3] & 0xFFFF0000u), true);
-      r0[q] = a;
-      r1[q] = c;
-    }
+    u32x4 r0, r1;
+    v_fp8_16(w, r0, r1);
     *reinterpret_cast<u32x4*>(p.v_codes + crow * kPage + qq) = r0;
     *reinterpret_cast<u32x4*>(p.v_codes + (crow + 1) * kPage + qq) = r1;
-    if (p.pv == 1) {   // BF16 rows: 16 keys of each channel, 32 bytes
-      uint32_t b0[8], b1[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        b0[j] = (w[2 * j] & 0xFFFFu) | (w[2 * j + 1] << 16);
-        b1[j] = (w[2 * j] >> 16) | (w[2 * j + 1] & 0xFFFF0000u);
-      }
-      uint16_t* a16 = reinterpret_cast<uint16_t*>(p.v_aux) + crow * kPage + qq;
-      *reinterpret_cast<u32x4*>(a16) = (u32x4){b0[0], b0[1], b0[2], b0[3]};
-      *reinterpret_cast<u32x4*>(a16 + 8) = (u32x4){b0[4], b0[5], b0[6], b0[7]};
-      *reinterpret_cast<u32x4*>(a16 + kPage) = (u32x4){b1[0], b1[1], b1[2], b1[3]};
-      *reinterpret_cast<u32x4*>(a16 + kPage + 8) = (u32x4){b1[4], b1[5], b1[6], b1[7]};
-    }
   }
-  if (p.pv == 2) {   // one NVFP4 group per channel: these 16 keys (absent ones zero)
-    float x0[16], x1[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) {
-      x0[j] = __uint_as_float(w[j] << 16);
-      x1[j] = __uint_as_float(w[j] & 0xFFFF0000u);
-    }
-    uint32_t sc0, sc1;
-    const uint64_t c0 = nvfp4_group(x0, 1.0f, rcp_sd, &sc0);
-    const uint64_t c1 = nvfp4_group(x1, 1.0f, rcp_sd, &sc1);
-    *reinterpret_cast<uint64_t*>(p.v_aux + crow * 32 + qq / 2) = c0;
-    *reinterpret_cast<uint64_t*>(p.v_aux + (crow + 1) * 32 + qq / 2) = c1;
-    p.v_aux[aux_scales + crow * 4 + qq / 16] = (uint8_t)sc0;
-    p.v_aux[aux_scales + (crow + 1) * 4 + qq / 16] = (uint8_t)sc1;
-  }
+  v_aux_16(p, w, crow, qq, page_run, rcp_sd);
 }
 
 // Parts of a head group's work, which need nothing of each other: separate
