@@ -766,22 +766,23 @@ __device__ __forceinline__ int item_rows(const PrefillParams& p, int b) {
   return share <= 1.15f * (float)longest ? kHalfRows : kItemRows;
 }
 
-// Block blk of ROWS rows of sequence b, head h, whose items have `rows` rows.  Items of
-// 128 rows are taken by the first block of each; of 256, by the first block of one of
-// their two halves, which of them changes every other item: the workgroups of an XCD are
-// dealt to its four shader engines in turn, and with the working ones eight apart all ran
-// on one of them (6000 rows behind 4000 tokens, 8:2 heads, 513 us; so 228).
+// Block blk of ROWS rows of sequence b, head h, whose items have `rows` rows.  An item is
+// taken by its last block, the first of them in dispatch order; in a call of one sequence
+// items of 256 rows by the last block of one of their halves, which of them changes every
+// other item: the workgroups of an XCD are dealt to its four shader engines in turn, and
+// with the working ones eight apart all ran on one of them (6000 rows behind 4000 tokens,
+// 8:2 heads, 513 us; so 228).
 template <int SEED, bool MX, int ROWS>
 __device__ __forceinline__ void prefill_pick_block(const PrefillParams& p, int b, int h, int blk, int rows,
                                                    PrefillSmemT<MX, kPvFp8>& sm) {
   constexpr int kPer = kHalfRows / ROWS;
-  if (blk % kPer != 0) return;
+  const int nq = p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b];
   int item = blk / kPer;
+  if (blk != min(item * kPer + kPer, (nq + ROWS - 1) / ROWS) - 1) return;
   if (rows == kItemRows) {
     const bool second = item & 1;
     item >>= 1;
-    const bool pick = (item >> 1) & 1;
-    const int nq = p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b];
+    const bool pick = p.batch > 1 || ((item >> 1) & 1);
     if (second != (pick && item * kItemRows + kHalfRows < nq)) return;
   }
   prefill_item<SEED, MX, kPvFp8>(p, b, h, item * rows, sm, rows);

@@ -292,7 +292,9 @@ __device__ __forceinline__ void prefill_split_item(const PrefillParams& p, int b
 // 16000 221 / 82, 256 behind 2000 40 / 25, 8:2 heads 1024 behind 16000 239 / 88, 2000
 // tokens 34.9 / 29.7 (MXFP4 28.7 / 23.1); not split: 1024 behind 16000 240 (split 340),
 // 500 behind 2000 43.7 (47.2), 1024-token prompt 22.3 (53.9), 256-token prompt 10.8
-// (17.7).
+// (17.7).  In a batch the count of blocks per unit is more than a split of one sequence
+// waits for, and the line stays at 2.65 (2.0) for either item: 40:8 heads, 91, 147 and 53
+// rows behind 155, 1928, 618 tokens 38.8 us at 1.75, 28.0 so.
 template <bool MX>
 struct FewSmem {
   union {
@@ -305,18 +307,29 @@ template <int SEED, bool MX>
 __device__ __forceinline__ void prefill_few_block(const PrefillParams& p, int bid, FewSmem<MX>& sm) {
   int b, h, rank;
   map_item(p, bid, b, h, rank);
-  // 32-row block: first those that begin 128 rows, the only ones with work where the
-  // tiles are not split
-  const int quads = p.n_qtiles / 4, rest = 4 * quads - 1 - rank;
-  const int blk = rank < quads ? 4 * (quads - 1 - rank) : rest / 3 * 4 + 1 + rest % 3;
   const int nq = p.cu_seqlens_q[b + 1] - p.cu_seqlens_q[b];
-  if (blk * kWaveRows >= nq) return;
+  const int blks = (nq + kWaveRows - 1) / kWaveRows;
+  // 32-row block, the last first; of one sequence first those that end 128 rows, the
+  // only ones with work where its tiles are not split (1300 tokens 32:8, wide table, 37
+  // -> 31 us; but 18, 506 and 401 rows behind 612, 611, 214 tokens 8:2 20.3 -> 24.2)
+  int blk = p.n_qtiles - 1 - rank;
+  if (p.batch == 1) {
+    const int quads = p.n_qtiles / 4;
+    if (rank < quads) {
+      blk = 4 * (quads - 1 - rank);
+      if (blk < blks) blk = min(blk + 3, blks - 1);
+    } else {
+      blk = blk / 3 * 4 + blk % 3;
+      if (blk == blks - 1) return;   // its last 128 rows are fewer: taken above
+    }
+  }
+  if (blk >= blks) return;
   int blocks = 0;   // 32-row blocks of one head over the batch
   for (int i = threadIdx.x & 63; i < p.batch; i += 64)
     blocks += (p.cu_seqlens_q[i + 1] - p.cu_seqlens_q[i] + kWaveRows - 1) / kWaveRows;
   const int per_cu = (wave_sum_all(blocks) * p.h_q + kComputeUnits - 1) / kComputeUnits;
   const int item = item_rows(p, b);
-  const float per_tile = item == kHalfRows ? (MX ? 1.45f : 1.75f) : (MX ? 2.0f : 2.65f);
+  const float per_tile = item == kHalfRows && p.batch == 1 ? (MX ? 1.45f : 1.75f) : (MX ? 2.0f : 2.65f);
   const float start = (float)p.q_start[b], rows = (float)nq;
   const float most = (start + rows) * (1.0f / kTile), mean = (start + 0.5f * rows) * (1.0f / kTile);
   const float split = MX ? 6.5f + 0.5f * mean : 7.5f + 0.625f * mean;

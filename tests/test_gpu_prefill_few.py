@@ -100,3 +100,16 @@ def test_mixed_step_same_bytes(orc, mp, total, new):
                              out=dec, partition_tokens=256, max_partitions=most), ws, mp.SMOOTH)
     torch.cuda.synchronize()
     assert np.array_equal(H.bits(out), ref) and np.array_equal(H.bits(dec), dec_ref)
+
+
+# maximum row counts above the call's: blocks of the grid past the rows, in one sequence
+# and in a batch
+@pytest.mark.parametrize("totals,new,most", [([900], [300], 1000), ([300], [1], 257), ([2000, 70], [33, 70], 640)])
+def test_fewer_rows_than_the_maximum(orc, mp, totals, new, most):
+    run = H.Run(orc, mp, 85, totals, 8, 2)
+    args, out = _check_chunks(run, new, mp.SMOOTH)
+    ref = H.bits(out)
+    out.fill_(float("nan"))
+    mp.prefill(**dict(args, max_seqlen_q=most), flags=mp.SMOOTH)
+    torch.cuda.synchronize()
+    assert np.array_equal(H.bits(out), ref)
