@@ -604,8 +604,8 @@ __device__ __forceinline__ void store_output(const PrefillParams& p, const ItemS
 // executed by a whole workgroup of eight waves, 32 rows each.
 //
 // What bounds it: the matrix pipe and the softmax's vector work on the same
-// SIMD, and, on long prefills, the card's power (MFMA alone on such operands
-// sustains 1.40 PFLOP/s FP16 and 3.7 PFLOP/s FP8 there).  Run one after the
+// SIMD, and, on long prefills, the card's power (large library products sustain
+// 1.07 PFLOP/s in FP16 and 3.1 in FP8 there).  Run one after the
 // other (QK, softmax, PV per tile, both waves of a SIMD in step at the tile
 // barrier) they leave the matrix pipe 40 % busy.  So step j is software
 // pipelined: the QK MFMAs of tile j-1 run among the exponentials of tile j,
@@ -615,9 +615,9 @@ __device__ __forceinline__ void store_output(const PrefillParams& p, const ItemS
 // 32x32 MFMAs take half the instructions and operand registers of the 16x16
 // ones, one query per lane halves the per-row softmax state, and constant LDS
 // offsets and buffer loads keep the address registers few enough for the whole
-// step to fit 256 registers.  Measured: 131072 tokens, 40:8 heads 134.1 -> 118.6
-// ms (matrix pipe 40 -> 48 % busy, clock 2.38 -> 2.24 GHz), 16384 tokens, 32:8
-// heads 1.79 -> 1.62 ms, MXFP4 65536 tokens, 40:8 heads 25.4 -> 22.0 ms.
+// step to fit 256 registers.  Measured on one card: 131072 tokens, 40:8 heads 133.8 ->
+// 121.4 ms (matrix pipe 40 -> 48 % busy, clock 2.38 -> 2.14 GHz), 16384 tokens, 32:8
+// heads 1.80 -> 1.65 ms, MXFP4 65536 tokens, 40:8 heads 25.4 -> 22.5 ms.
 //
 // LDS buffers: K(j-1) and V(j) are read in step j; K(j-2) is stored over K(j)
 // and V(j-1) over V(j+1), both read in step j+1, before its barrier.
